@@ -48,7 +48,8 @@ struct ScanParams {
   int64_t chunk;  // tokens per time chunk
   int64_t h0_stride, hT_stride;
   int nchunks;    // C
-  int dblocks;    // ceil(D / 256)
+  int threads;    // workgroup size of the scan kernels, kScanThreads or less
+  int dblocks;    // workgroups covering the D channels
   int flags;
 };
 

@@ -14,7 +14,7 @@ hipError_t launch_query_scan(const ScanParams& p, const RetrieveParams& rp, int 
   const bf16_t* BB = static_cast<const bf16_t*>(p.Bm);
   const bf16_t* CC = static_cast<const bf16_t*>(p.Cm);
   const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(p.dblocks) * p.B));
-  const dim3 block(kSBlock);
+  const dim3 block(static_cast<unsigned>(p.threads));
   if (p.y != nullptr && (p.flags & kHasZ)) {
     if (out_dtype == 0 && state_dtype == 0)
       hipLaunchKernelGGL((query_scan_kernel<16, bf16_t, float, float, kReadout, true>), grid, block, 0,

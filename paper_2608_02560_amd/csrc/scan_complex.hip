@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
   const int64_t D = p.D;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int64_t wave_d0 = static_cast<int64_t>(dblk) * kSBlock + wave * 64;
+  const int64_t wave_d0 = static_cast<int64_t>(dblk) * p.threads + wave * 64;
   // progress balancing between the two waves of a SIMD (scan_kernels.h)
   const bool fair = balance_enabled(p);
   __shared__ int progress[kSWaves];
@@ -284,21 +284,21 @@ hipError_t launch_c(const ScanParams& p, hipStream_t s) {
   if (p.nchunks > 1) {
     const dim3 g1(static_cast<unsigned>(rows_blocks * (p.nchunks - 1)));
     hipLaunchKernelGGL((scan_complex_kernel<N, TIn, float, float, kSummary, false>), g1,
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
     const int64_t lanes = p.B * p.D * N;
     hipLaunchKernelGGL((complex_carry_kernel<TSt>), dim3(static_cast<unsigned>((lanes + 255) / 256)),
                        dim3(256), 0, s, p, N);
   }
   const dim3 grid(static_cast<unsigned>(rows_blocks * p.nchunks));
   if (p.y != nullptr && (p.flags & kHasZ))
-    hipLaunchKernelGGL((scan_complex_kernel<N, TIn, TOut, TSt, kReadout, true>), grid, dim3(kSBlock),
+    hipLaunchKernelGGL((scan_complex_kernel<N, TIn, TOut, TSt, kReadout, true>), grid, dim3(p.threads),
                        0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
   else if (p.y != nullptr)
     hipLaunchKernelGGL((scan_complex_kernel<N, TIn, TOut, TSt, kReadout, false>), grid,
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
   else
     hipLaunchKernelGGL((scan_complex_kernel<N, TIn, float, TSt, kStateOnly, false>), grid,
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
   return hipGetLastError();
 }
 

@@ -418,7 +418,6 @@ __device__ __forceinline__ void scan_body(
   constexpr int P = kLanesPerChannel<N>;
   constexpr int NL = N / P;                // states held by one lane
   constexpr int G = (NL + 15) / 16;        // registers per token for B_t (and C_t)
-  constexpr int kChan = kSBlock / P;       // channels per workgroup
   constexpr int kPF = TRAJ != 0 ? kPFWide : kPFPlain;
   constexpr bool kRead = KIND == kReadout;
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
@@ -431,7 +430,7 @@ __device__ __forceinline__ void scan_body(
   const int wave = threadIdx.x >> 6;
   const int grp = (lane >> 4) % P;  // this lane's state group
   // channel of this lane: 16 per row, rows of one channel set are P apart
-  const int64_t wave_d0 = static_cast<int64_t>(dblk) * kChan + wave * (64 / P);
+  const int64_t wave_d0 = static_cast<int64_t>(dblk) * (p.threads / P) + wave * (64 / P);
 
   // progress balancing: see balance_step
   const bool fair = balance_enabled(p);
@@ -929,13 +928,13 @@ hipError_t launch_final(const ScanParams& p, int64_t g3, hipStream_t s) {
   const TIn* CC = static_cast<const TIn*>(p.Cm);
   if (p.y != nullptr && (p.flags & kHasZ))
     hipLaunchKernelGGL((scan_kernel<N, TIn, TOut, TSt, kReadout, true, TRAJ>), dim3(static_cast<unsigned>(g3)),
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
   else if (p.y != nullptr)
     hipLaunchKernelGGL((scan_kernel<N, TIn, TOut, TSt, kReadout, false, TRAJ>), dim3(static_cast<unsigned>(g3)),
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<TOut*>(p.y), p);
   else
     hipLaunchKernelGGL((scan_kernel<N, TIn, float, TSt, kStateOnly, false, TRAJ>), dim3(static_cast<unsigned>(g3)),
-                       dim3(kSBlock), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
+                       dim3(p.threads), 0, s, X, DT, Z, BB, CC, static_cast<float*>(nullptr), p);
   return hipGetLastError();
 }
 
@@ -945,7 +944,7 @@ hipError_t launch_typed(const ScanParams& p, hipStream_t s) {
   if (p.nchunks > 1) {
     const int64_t g1 = rows_blocks * (p.nchunks - 1);
     hipLaunchKernelGGL((scan_kernel<N, TIn, float, float, kSummary, false, 0>), dim3(static_cast<unsigned>(g1)),
-                       dim3(kSBlock), 0, s, static_cast<const TIn*>(p.x), static_cast<const TIn*>(p.dt),
+                       dim3(p.threads), 0, s, static_cast<const TIn*>(p.x), static_cast<const TIn*>(p.dt),
                        static_cast<const TIn*>(p.z), static_cast<const TIn*>(p.Bm),
                        static_cast<const TIn*>(p.Cm), static_cast<float*>(nullptr), p);
     const int64_t lanes = p.B * p.D * N;
