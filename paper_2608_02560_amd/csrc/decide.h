@@ -40,6 +40,7 @@ constexpr int kBList = 512;           // surviving-block list capacity (>= 2 gro
 constexpr float kMaxNorm2 = 60000.f;
 constexpr int kRowWords = 8192;       // LDS words for staged candidate rows
 constexpr int kCacheGroups = 2;       // 256-block groups whose maxima stay in registers
+constexpr int kWideCache = 16;         // the same of several waves, 64-block groups per wave
 
 // LDS of one deciding wave.  The query in fp64 takes the first E doubles
 // of `qr`; the staged candidate rows take the rest (so a short query leaves
@@ -51,6 +52,32 @@ struct DecideShared {
   int blist[kBList];
   double slot_s[64];
   int slot_i[64];
+};
+
+// LDS of a decision by NW waves (DecideWide), besides wave 0's DecideShared.
+// Wave 0 decides as a lone wave does; the others share the passes over the
+// block maxima and the whole-block rescorings.  Every lane takes the largest
+// maximum of its blocks, and t_k is the k-th largest of those 64 NW values:
+// the maxima of k distinct blocks reach it, which is all the bound needs, and
+// one pass over the maxima finds it whatever k is (the lone wave's k rounds
+// took 22 us for k = 10 over 100,003 keys).  With few blocks the second
+// maxima are entries of their own, which keeps t_k close to the k-th largest
+// score.  Each wave then tests its blocks and leaves one bit per block; from
+// there the others serve wave 0: between two barriers all rescore the blocks
+// it listed (flist), each wave a share of the features (a block by one wave
+// took 6 us, two dependent rounds of 24 loads).  Any valid t_k gives the same
+// results.
+constexpr int kMaskWords = 512;  // 64-block groups per round of block tests
+constexpr int kRescore = 8;      // blocks rescored between two barriers
+template <int NW>
+struct DecideWide {
+  float lmax[NW * 64];      // the lanes' largest entries
+  float nmax[NW];           // largest block norm of the wave's blocks
+  float qnorm2;
+  uint64_t mask[kMaskWords];
+  int flist[kRescore];      // blocks to rescore
+  float fpart[kRescore][NW][kKB];  // the waves' shares of their keys' scores
+  int nfull;                // blocks listed; negative: the query is decided
 };
 
 // The deciding wave's lanes exchange values through LDS: a compiler barrier
@@ -78,10 +105,12 @@ __device__ __forceinline__ void wave_sync() {
 // list.
 // FL: row loads in flight per round when a whole block is rescored in fp32
 // (as many as the caller's register budget allows).
-template <int FL>
-__device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t q,
-                                                DecideShared& sh) {
+// NW: waves deciding together (`wd` is their common LDS); all call this.
+template <int FL, int NW = 1>
+__device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t q, DecideShared& sh,
+                                                DecideWide<NW>* wd = nullptr) {
   const int lane = threadIdx.x & 63;
+  const int wave = NW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int E = static_cast<int>(p.E);
   const int nkb = p.nkb;
   const int k = p.k;
@@ -99,25 +128,24 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
   const float* bsec = p.blocksec + q * nkb;
   const uint8_t* barg = p.blockarg + q * nkb;
 
-  // the block maxima and norms of the first kCacheGroups x 256 blocks,
-  // loaded once (in flight with the query row) and held in registers for
-  // the t_k rounds and the block tests; blocks past nkb hold NaN / 0
-  float cb[4 * kCacheGroups], cn[4 * kCacheGroups];
+  // the block maxima and norms of the first kCacheGroups x 256 blocks (NW > 1:
+  // of the first kWideCache x 64 NW), loaded once (in flight with the query
+  // row) and held in registers for t_k and the block tests; blocks past nkb
+  // hold NaN / 0.  64-block groups are dealt to the waves in turn.
+  constexpr int kCached = NW > 1 ? kWideCache : 4 * kCacheGroups;
+  float cb[kCached], cn[kCached];
 #pragma unroll
-  for (int g = 0; g < kCacheGroups; ++g) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int kb = 256 * g + 64 * j + lane;
-      cb[4 * g + j] = kb < nkb ? bm[kb] : __builtin_nanf("");
-      cn[4 * g + j] = kb < nkb ? p.blocknorm2[kb] : 0.f;
-    }
+  for (int c = 0; c < kCached; ++c) {
+    const int kb = 64 * (NW * c + wave) + lane;
+    cb[c] = kb < nkb ? bm[kb] : __builtin_nanf("");
+    cn[c] = kb < nkb ? p.blocknorm2[kb] : 0.f;
   }
 
   // fixed-width groups of predicated loads, so every load of a group is in
   // flight before the first is consumed
   const int e4n = E / 4;
   float nq = 0.f;
-  for (int g0 = 0; g0 < e4n; g0 += 4 * 64) {
+  for (int g0 = 0; g0 < e4n && wave == 0; g0 += 4 * 64) {
     float4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -134,56 +162,111 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
       nq = fmaf(v[u].x, v[u].x, fmaf(v[u].y, v[u].y, fmaf(v[u].z, v[u].z, fmaf(v[u].w, v[u].w, nq))));
     }
   }
-  const float qnorm2 = wave_sum(nq);
-  const float qnorm = sqrtf(qnorm2);
+  float qnorm2 = wave_sum(nq);
+  if constexpr (NW > 1) {
+    if (wave == 0 && lane == 0) wd->qnorm2 = qnorm2;
+  }
 
   // t_k: k rounds, each taking the first (value, index) pair after the
   // previous one (the first round also takes the largest block norm); fewer
   // than k ranked blocks leave t_k = -inf (every key is then a candidate)
   float nmax = 0.f;
 #pragma unroll
-  for (int c = 0; c < 4 * kCacheGroups; ++c) nmax = fmaxf(nmax, cn[c]);
+  for (int c = 0; c < kCached; ++c) nmax = fmaxf(nmax, cn[c]);
   float tv = INFINITY;
-  int ti = -1;
   bool found = true;
-  for (int r = 0; r < k && found; ++r) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    bool any = false;
-    auto consider = [&](float b, int kb) {
-      if (before(tv, ti, b, kb) && (!any || before(b, kb, bv, bi))) {
-        bv = b;
-        bi = kb;
-        any = true;
-      }
-    };
+  if constexpr (NW > 1) {
+    float lm = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < 4 * kCacheGroups; ++c) consider(cb[c], 64 * c + lane);
-    for (int kb0 = 256 * kCacheGroups; kb0 < nkb; kb0 += 256) {
-      float b[4], n[4];
+    for (int c = 0; c < kCached; ++c) lm = fmaxf(lm, cb[c]);  // NaN is not ranked
+    constexpr int kU = 8;
+    for (int g = NW * kCached + wave; 64 * g < nkb; g += NW * kU) {
+      float b[kU], n[kU];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int kb = kb0 + 64 * j + lane;
-        b[j] = kb < nkb ? bm[kb] : __builtin_nanf("");
-        n[j] = (r == 0 && kb < nkb) ? p.blocknorm2[kb] : 0.f;
+      for (int u = 0; u < kU; ++u) {
+        const int kb = 64 * (g + NW * u) + lane;
+        b[u] = kb < nkb ? bm[kb] : -INFINITY;
+        n[u] = kb < nkb ? p.blocknorm2[kb] : 0.f;
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        nmax = fmaxf(nmax, n[j]);
-        consider(b[j], kb0 + 64 * j + lane);
+      for (int u = 0; u < kU; ++u) {
+        lm = fmaxf(lm, b[u]);
+        nmax = fmaxf(nmax, n[u]);
       }
     }
-    // the wave's first pair: the largest value, then the lowest index among
-    // the lanes holding it (lanes without a pair take no part)
-    const float m = wave_max(any ? bv : -INFINITY);
-    const int mi = wave_min(any && bv == m ? bi : 0x7fffffff);
-    found = __ballot(any) != 0;
-    if (found) {
-      tv = m;
-      ti = mi;
+    // up to 32 NW blocks: the second maxima, in the lanes that hold no block
+    const int extra = 64 * wave + lane - 32 * NW;
+    if (nkb <= 32 * NW && extra >= 0 && extra < nkb) lm = fmaxf(lm, bsec[extra]);
+    wd->lmax[64 * wave + lane] = lm;
+    nmax = wave_max(nmax);
+    if (lane == 0) wd->nmax[wave] = nmax;
+    __syncthreads();
+    qnorm2 = wd->qnorm2;
+    float v[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      nmax = fmaxf(nmax, wd->nmax[w]);
+      v[w] = wd->lmax[64 * w + lane];
     }
+    // k rounds, each taking the largest value left
+    for (int r = 0; r < k; ++r) {
+      float m = v[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) m = fmaxf(m, v[w]);
+      tv = wave_max(m);
+      if (lane == __builtin_ctzll(__ballot(m == tv))) {
+        bool gone = false;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          if (!gone && v[w] == tv) {
+            v[w] = -INFINITY;
+            gone = true;
+          }
+        }
+      }
+    }
+  } else {
+    int ti = -1;
+    for (int r = 0; r < k && found; ++r) {
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+      bool any = false;
+      auto consider = [&](float b, int kb) {
+        if (before(tv, ti, b, kb) && (!any || before(b, kb, bv, bi))) {
+          bv = b;
+          bi = kb;
+          any = true;
+        }
+      };
+#pragma unroll
+      for (int c = 0; c < kCached; ++c) consider(cb[c], 64 * c + lane);
+      for (int kb0 = 256 * kCacheGroups; kb0 < nkb; kb0 += 256) {
+        float b[4], n[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int kb = kb0 + 64 * j + lane;
+          b[j] = kb < nkb ? bm[kb] : __builtin_nanf("");
+          n[j] = (r == 0 && kb < nkb) ? p.blocknorm2[kb] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          nmax = fmaxf(nmax, n[j]);
+          consider(b[j], kb0 + 64 * j + lane);
+        }
+      }
+      // the wave's first pair: the largest value, then the lowest index among
+      // the lanes holding it (lanes without a pair take no part)
+      const float m = wave_max(any ? bv : -INFINITY);
+      const int mi = wave_min(any && bv == m ? bi : 0x7fffffff);
+      found = __ballot(any) != 0;
+      if (found) {
+        tv = m;
+        ti = mi;
+      }
+    }
+    nmax = wave_max(nmax);
   }
-  nmax = wave_max(nmax);
+  const float qnorm = sqrtf(qnorm2);
   const float tk = found ? tv : -INFINITY;
 
   // Screen-score error bound e(i) = g |q| |k_i| + h (|q| + |k_i|) + tiny;
@@ -306,6 +389,69 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
     ncand = 0;
   };
 
+  // fp32 scores of block kb's keys (lane l: key 32 kb + l mod 32) over this
+  // wave's share of the features
+  auto rescore = [&](int kb) __attribute__((always_inline)) {
+    const int64_t b0 = static_cast<int64_t>(kb) * kKB;
+    const int cnt = static_cast<int>(p.M - b0 < kKB ? p.M - b0 : kKB);
+    const int r = lane & (kKB - 1);
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    if (r < cnt) {
+      // FL 16-byte loads of the row in flight per round (the sum's
+      // order is free: any order stays within gamma_{E+1})
+      constexpr int kStep = 2 * NW;
+      const float4* row = reinterpret_cast<const float4*>(p.K + (b0 + r) * p.E);
+      for (int e0 = 2 * wave + (lane >> 5); e0 < e4n; e0 += kStep * FL) {
+        float4 v[FL];
+#pragma unroll
+        for (int u = 0; u < FL; ++u) {
+          const int f = e0 + kStep * u;
+          v[u] = f < e4n ? row[f] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < FL; ++u) {
+          const int f = e0 + kStep * u;
+          if (f < e4n) {
+            const double2 q01 = *reinterpret_cast<const double2*>(qs + 4 * f);
+            const double2 q23 = *reinterpret_cast<const double2*>(qs + 4 * f + 2);
+            float& a = part[u & 3];
+            a = fmaf(static_cast<float>(q01.x), v[u].x, a);
+            a = fmaf(static_cast<float>(q01.y), v[u].y, a);
+            a = fmaf(static_cast<float>(q23.x), v[u].z, a);
+            a = fmaf(static_cast<float>(q23.y), v[u].w, a);
+          }
+        }
+      }
+    }
+    const float tot = (part[0] + part[1]) + (part[2] + part[3]);
+    return tot + xor_shfl(tot, 32);
+  };
+  // the keys of block kb (bit r: key 32 kb + r) that pass the test with those
+  auto passing = [&](int kb, float tot) {
+    const int64_t key = static_cast<int64_t>(kb) * kKB + lane;
+    return __ballot(lane < kKB && key < p.M &&
+                    (exhaustive || static_cast<double>(tot) + err(p.rownorm2[key]) >= thresh));
+  };
+  // this wave's share of the listed blocks (NW > 1)
+  auto share = [&](int nf) {
+    if constexpr (NW > 1) {
+      for (int f = 0; f < nf; ++f) {
+        const float t = rescore(wd->flist[f]);
+        if (lane < kKB) wd->fpart[f][wave][lane] = t;
+      }
+    }
+  };
+  auto add_keys = [&](int kb, uint64_t cmask) {
+    if (cmask) {
+      if (ncand + kKB > kCand) {
+        early = true;
+        flush();
+      }
+      if (cmask >> lane & 1) cand[ncand + __builtin_popcountll(cmask & ((1ull << lane) - 1))] = kb * kKB + lane;
+      ncand += __builtin_popcountll(cmask);
+    }
+  };
+
   // Surviving blocks go, in ascending order, to an LDS list, tested 64 per
   // round (lane j takes entry i0 + j, its summary loads in flight together
   // with the other lanes').  A key other than the block's largest has a
@@ -343,54 +489,34 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
         ncand += __builtin_popcountll(smask);
       }
       uint64_t fmask = __ballot(full);
+      if constexpr (NW > 1) {
+        // the waves rescore the round's blocks together
+        while (fmask) {
+          int nf = 0;
+          for (; fmask && nf < kRescore; ++nf) {
+            const int fb = __builtin_amdgcn_readlane(kb, __builtin_ctzll(fmask));
+            fmask &= fmask - 1;
+            if (lane == 0) wd->flist[nf] = fb;
+          }
+          if (lane == 0) wd->nfull = nf;
+          __syncthreads();
+          share(nf);
+          __syncthreads();
+          for (int f = 0; f < nf; ++f) {
+            float tot = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) tot += wd->fpart[f][w][lane & (kKB - 1)];
+            const int fb = wd->flist[f];
+            add_keys(fb, passing(fb, tot));
+          }
+        }
+        continue;
+      }
       while (fmask) {
         const int j = __builtin_ctzll(fmask);
         fmask &= fmask - 1;
-        const int64_t b0 = static_cast<int64_t>(__builtin_amdgcn_readlane(kb, j)) * kKB;
-        const int cnt = static_cast<int>(p.M - b0 < kKB ? p.M - b0 : kKB);
-        const int r = lane & (kKB - 1);
-        const bool kok = r < cnt;
-        float part[4] = {0.f, 0.f, 0.f, 0.f};
-        if (kok) {
-          // FL 16-byte loads of the row in flight per round (the sum's
-          // order is free: any order stays within gamma_{E+1})
-          const float4* row = reinterpret_cast<const float4*>(p.K + (b0 + r) * p.E);
-          for (int e0 = lane >> 5; e0 < e4n; e0 += 2 * FL) {
-            float4 v[FL];
-#pragma unroll
-            for (int u = 0; u < FL; ++u) {
-              const int f = e0 + 2 * u;
-              v[u] = f < e4n ? row[f] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < FL; ++u) {
-              const int f = e0 + 2 * u;
-              if (f < e4n) {
-                const double2 q01 = *reinterpret_cast<const double2*>(qs + 4 * f);
-                const double2 q23 = *reinterpret_cast<const double2*>(qs + 4 * f + 2);
-                float& a = part[u & 3];
-                a = fmaf(static_cast<float>(q01.x), v[u].x, a);
-                a = fmaf(static_cast<float>(q01.y), v[u].y, a);
-                a = fmaf(static_cast<float>(q23.x), v[u].z, a);
-                a = fmaf(static_cast<float>(q23.y), v[u].w, a);
-              }
-            }
-          }
-        }
-        float tot = (part[0] + part[1]) + (part[2] + part[3]);
-        tot += xor_shfl(tot, 32);
-        const bool ok = lane < kKB && kok &&
-                        (exhaustive || static_cast<double>(tot) +
-                                           err(p.rownorm2[b0 + r]) >= thresh);
-        const uint64_t cmask = __ballot(ok);
-        if (cmask) {
-          if (ncand + kKB > kCand) {
-            early = true;
-            flush();
-          }
-          if (ok) cand[ncand + __builtin_popcountll(cmask & ((1ull << lane) - 1))] = static_cast<int>(b0 + r);
-          ncand += __builtin_popcountll(cmask);
-        }
+        const int fb = __builtin_amdgcn_readlane(kb, j);
+        add_keys(fb, passing(fb, rescore(fb)));
       }
     }
     wave_sync();  // every list entry is read before the list is refilled
@@ -409,6 +535,66 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
       nbl += __builtin_popcountll(bmask);
     }
   };
+  if constexpr (NW > 1) {
+    constexpr int kRound = 64 * kMaskWords;  // blocks per round
+    for (int s0 = 0; s0 < nkb; s0 += kRound) {
+      const int s1 = nkb - s0 < kRound ? nkb : s0 + kRound;
+      const int words = (s1 - s0 + 63) / 64;
+      auto test = [&](int i, float b, float n) {
+        const uint64_t bmask = __ballot(s0 + 64 * i + lane < s1 &&
+                                        (exhaustive || static_cast<double>(b) + err(n) >= thresh));
+        if (lane == 0 && i < words) wd->mask[i] = bmask;
+      };
+      int w0 = wave;
+      if (s0 == 0) {
+#pragma unroll
+        for (int c = 0; c < kCached; ++c)
+          if (NW * c < words) test(NW * c + wave, cb[c], cn[c]);
+        w0 += NW * kCached;
+      }
+      constexpr int kU = 8;  // words in flight
+      for (int i0 = w0; i0 < words; i0 += kU * NW) {
+        float b[kU], n[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int kb = s0 + 64 * (i0 + u * NW) + lane;
+          b[u] = kb < s1 ? bm[kb] : -INFINITY;
+          n[u] = kb < s1 ? p.blocknorm2[kb] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) test(i0 + u * NW, b[u], n[u]);
+      }
+      __syncthreads();
+      if (wave == 0) {
+        for (int i0 = 0; i0 < words; i0 += 64) {
+          const uint64_t mine = i0 + lane < words ? wd->mask[i0 + lane] : 0;
+          uint64_t some = __ballot(mine != 0);
+          while (some) {
+            const int j = __builtin_ctzll(some);
+            some &= some - 1;
+            const uint64_t bmask = wd->mask[i0 + j];
+            if (nbl > kBList - 64) test_list();
+            if (bmask >> lane & 1)
+              blist[nbl + __builtin_popcountll(bmask & ((1ull << lane) - 1))] = s0 + 64 * (i0 + j) + lane;
+            nbl += __builtin_popcountll(bmask);
+          }
+        }
+        if (nbl > 0) test_list();
+        if (lane == 0) wd->nfull = -1;
+        __syncthreads();
+      } else {
+        // serve wave 0's rescorings until it is done with the round
+        for (;;) {
+          __syncthreads();
+          const int nf = wd->nfull;
+          if (nf < 0) break;
+          share(nf);
+          __syncthreads();
+        }
+      }
+    }
+    if (wave != 0) return 0;
+  } else {
 #pragma unroll
   for (int g = 0; g < kCacheGroups; ++g) {
     if (256 * g < nkb) {
@@ -426,6 +612,7 @@ __device__ __forceinline__ int32_t decide_query(const RetrieveParams& p, int64_t
       n4[j] = kb < nkb ? p.blocknorm2[kb] : 0.f;
     }
     add_group(kb0, b4, n4);
+  }
   }
   if (nbl > 0) test_list();
   // Top-1 without scores: the candidate list provably holds the exact

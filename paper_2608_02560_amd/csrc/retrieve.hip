@@ -85,6 +85,33 @@ __global__ __launch_bounds__(256) void prep_kernel(const RetrieveParams p) {
   reinterpret_cast<halfx8*>(p.qop)[t] = o8;
 }
 
+// Running largest value m1 (row i1) and largest of the others m2; a tie with
+// m1 goes to m2.
+__device__ __forceinline__ void block_top2(float v, int row, float& m1, float& m2, int& i1) {
+  if (v > m1) {
+    m2 = m1;
+    m1 = v;
+    i1 = row;
+  } else {
+    m2 = fmaxf(m2, v);
+  }
+}
+
+// Merges the two lane halves' summaries of block kb for query q (each holds
+// 16 of the block's rows) and stores the result.
+__device__ __forceinline__ void store_summary(const RetrieveParams& p, int64_t q, int half, int64_t kb, float m1,
+                                              float m2, int i1) {
+  const float o1 = xor_shfl(m1, 32);
+  const float o2 = xor_shfl(m2, 32);
+  const int oi = __builtin_bit_cast(int, xor_shfl(__builtin_bit_cast(float, i1), 32));
+  const bool mine = m1 > o1 || (m1 == o1 && i1 < oi);
+  if (half == 0 && q < p.Q && kb < p.nkb) {
+    p.blockmax[q * p.nkb + kb] = mine ? m1 : o1;
+    p.blocksec[q * p.nkb + kb] = mine ? fmaxf(m2, o1) : fmaxf(o2, m1);
+    p.blockarg[q * p.nkb + kb] = static_cast<uint8_t>(mine ? i1 : oi);
+  }
+}
+
 // screen: workgroup (kg, qg) = key blocks [kRetBlocks kg, kRetBlocks kg +
 // kRetBlocks) (32 keys each) x query groups [kRetWaves qg, kRetWaves qg +
 // kRetWaves) (32 queries each), wave w taking query group kRetWaves qg + w.
@@ -248,35 +275,15 @@ __global__ __launch_bounds__(64 * kRetWaves) void screen_kernel(const RetrievePa
 #pragma unroll
     for (int b = 0; b < kRetBlocks; ++b) {
       const int64_t kb = static_cast<int64_t>(kg) * kRetBlocks + b;
-      // largest (m1, its key i1) and the largest of the other keys (m2) over
-      // this lane's 16 rows; a tie with m1 goes to m2, keys past M rank last
+      // over this lane's 16 rows; keys past M rank last
       float m1 = -INFINITY, m2 = -INFINITY;
       int i1 = 0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = 8 * (r >> 2) + 4 * half + (r & 3);
-        const float v = kb * kKB + row < p.M ? acc[b][r] * kUnscale : -INFINITY;
-        if (v > m1) {
-          m2 = m1;
-          m1 = v;
-          i1 = row;
-        } else {
-          m2 = fmaxf(m2, v);
-        }
+        block_top2(kb * kKB + row < p.M ? acc[b][r] * kUnscale : -INFINITY, row, m1, m2, i1);
       }
-      // merge with the other half's (rows 4 apart in each group of 8)
-      const float o1 = xor_shfl(m1, 32);
-      const float o2 = xor_shfl(m2, 32);
-      const int oi = __builtin_bit_cast(int, xor_shfl(__builtin_bit_cast(float, i1), 32));
-      const bool mine = m1 > o1 || (m1 == o1 && i1 < oi);
-      const float s1 = mine ? m1 : o1;
-      const float s2 = mine ? fmaxf(m2, o1) : fmaxf(o2, m1);
-      const int si = mine ? i1 : oi;
-      if (half == 0 && q < p.Q && kb < p.nkb) {
-        p.blockmax[q * p.nkb + kb] = s1;
-        p.blocksec[q * p.nkb + kb] = s2;
-        p.blockarg[q * p.nkb + kb] = static_cast<uint8_t>(si);
-      }
+      store_summary(p, q, half, kb, m1, m2, i1);
     }
   }
   // squared key norms (workgroups with qg == 0; a prepared index holds
@@ -359,13 +366,18 @@ __global__ __launch_bounds__(64) void prep_norms_kernel(const RetrieveParams p) 
   if (lane == 0) p.blocknorm2[kb] = mx;
 }
 
-// FL: row loads in flight when a whole block is rescored.  Top-1 keeps 16
-// (24 took its decision from 7.1 to 7.5 us: more registers on its short
-// path); top-k, which rescores whole blocks more often, takes 24.
-template <int FL>
-__global__ __launch_bounds__(64) void decide_kernel(const RetrieveParams p) {
+// FL: row loads in flight when a whole block is rescored: 16 for a lone wave
+// (24 took its decision from 7.1 to 7.5 us: more registers on its short path),
+// 12 for each of four, one round of a 384-feature row.
+template <int FL, int NW>
+__global__ __launch_bounds__(64 * NW) void decide_kernel(const RetrieveParams p) {
   __shared__ DecideShared sh;
-  decide_query<FL>(p, blockIdx.x, sh);
+  if constexpr (NW > 1) {
+    __shared__ DecideWide<NW> wd;
+    decide_query<FL, NW>(p, blockIdx.x, sh, &wd);
+  } else {
+    decide_query<FL>(p, blockIdx.x, sh);
+  }
 }
 
 }  // namespace
@@ -420,10 +432,16 @@ hipError_t launch_retrieve_screen(RetrieveParams& p, hipStream_t s) {
 }
 
 hipError_t launch_retrieve_decide(const RetrieveParams& p, hipStream_t s) {
-  if (p.k == 1)
-    hipLaunchKernelGGL(decide_kernel<16>, dim3(static_cast<unsigned>(p.Q)), dim3(64), 0, s, p);
+  const dim3 grid(static_cast<unsigned>(p.Q));
+  // Four waves a query where the passes over the block maxima or the block
+  // rescorings count: top-k (256 x 10,000 x 384, k = 3: slowest query 16.4 ->
+  // 13.8 us; 1 x 500, k = 10: 40 -> 19 us) and indexes whose maxima a lone
+  // wave cannot hold in registers (16 x 100,003, k = 3: 41 -> 14 us).  The
+  // short top-1 decision (7 us) gains nothing from more waves.
+  if (p.k > 1 || p.nkb > 256 * kCacheGroups)
+    hipLaunchKernelGGL((decide_kernel<12, 4>), grid, dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL(decide_kernel<24>, dim3(static_cast<unsigned>(p.Q)), dim3(64), 0, s, p);
+    hipLaunchKernelGGL((decide_kernel<16, 1>), grid, dim3(64), 0, s, p);
   return hipGetLastError();
 }
 
