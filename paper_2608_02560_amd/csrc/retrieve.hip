@@ -315,6 +315,135 @@ __global__ __launch_bounds__(64 * kRetWaves) void screen_kernel(const RetrievePa
   }
 }
 
+// Screen for at most 32 queries (one 32-column tile).  The 256-query screen
+// gives each workgroup 8 waves of queries; with one group of queries seven of
+// them only stage keys, one workgroup fits a CU (216 VGPRs), and the keys
+// stream at 2.7 TB/s (16 x 100,003 x 384, prepared: 28 us for 77 MB).  Here a
+// workgroup of kFewWaves waves takes one block of 32 keys at a time and splits
+// its features: wave w multiplies steps [w NS', (w + 1) NS') of every block
+// with query operands that it rounds once and keeps in registers, reading its
+// key operands straight from memory into registers, so there is no staging,
+// no query-rounding launch and one round trip per block; the partial sums meet
+// in LDS (two buffers, one barrier per block), where one wave, another one
+// for each block, forms the block's summary.  Any split of the fp32 sum stays
+// within the margin's 2 gamma_E.  Bound by the key stream: several workgroups
+// per CU keep it going.  16 x 100,003 x 384 prepared: rounding and screen
+// 3.0 + 27.9 -> 21.8 us (3.5 TB/s); 4 x 3,000: 3 + 8 -> 4.8 us.
+constexpr int kFewWaves = 4;
+constexpr int kFewQ = 32;
+constexpr int kFewMaxE = 1024;  // kFewWaves x 16 steps of 16 features
+
+template <bool PREP, int NS>
+__global__ __launch_bounds__(64 * kFewWaves, NS <= 8 ? 4 : 2) void screen_few_kernel(const RetrieveParams p) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31;
+  const int half = lane >> 5;
+  const int E = static_cast<int>(p.E);
+  const int per = (p.nks + kFewWaves - 1) / kFewWaves;  // steps per wave, <= NS
+  const int ks0 = wave * per;
+  const int n = p.nks - ks0 < per ? p.nks - ks0 : per;  // this wave's steps (may be <= 0)
+
+  __shared__ float part[2][kFewWaves][16][64];
+  __shared__ float norm[2][kFewWaves][64];
+
+  // eight features of a row from feature e on (fp32), zero past E
+  auto row8 = [&](const __amdgpu_buffer_rsrc_t r, uint32_t row, bool ok, int e, float4 (&v)[2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const uint32_t off = ok && e + 4 * c < E ? (row * static_cast<uint32_t>(E) + e + 4 * c) * 4u : kDropOffset;
+      v[c] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    }
+  };
+  auto to_op8 = [&](const float4 (&v)[2]) {
+    const halfx4 a = to_op(v[0]), b = to_op(v[1]);
+    return halfx8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  };
+
+  // query operands of this wave's steps
+  halfx8 aq[NS];
+  const __amdgpu_buffer_rsrc_t qres = make_rsrc(p.q, static_cast<uint32_t>(p.Q * E * 4));
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    float4 v[2];
+    row8(qres, static_cast<uint32_t>(r32), i < n && r32 < p.Q, 16 * (ks0 + i) + 8 * half, v);
+    aq[i] = to_op8(v);
+  }
+
+  int it = 0;
+  for (int64_t kb = blockIdx.x; kb < p.nkb; kb += gridDim.x, ++it) {
+    const int buf = it & 1;
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    if constexpr (PREP) {
+      const halfx8* src = static_cast<const halfx8*>(p.kop) + (kb * p.nks + ks0) * 64 + 32 * half;
+      halfx8 kv[NS];
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+        kv[i] = i < n ? src[64 * i + (r32 ^ ((2 * ((ks0 + i) % kKS) + half) & 31))] : halfx8{};
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+        if (i < n) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kv[i], aq[i], acc, 0, 0, 0);
+    } else {
+      const int64_t k0 = kb * kKB;
+      const uint32_t rows = static_cast<uint32_t>(p.M - k0 < kKB ? p.M - k0 : kKB);
+      const __amdgpu_buffer_rsrc_t kres = make_rsrc(p.K + k0 * E, rows * static_cast<uint32_t>(E) * 4u);
+      float n2 = 0.f;
+      constexpr int kG = NS < 8 ? NS : 8;  // steps in flight
+#pragma unroll
+      for (int g = 0; g < NS; g += kG) {
+        float4 kf[kG][2];
+#pragma unroll
+        for (int i = 0; i < kG; ++i)
+          row8(kres, static_cast<uint32_t>(r32), g + i < n && static_cast<uint32_t>(r32) < rows,
+               16 * (ks0 + g + i) + 8 * half, kf[i]);
+#pragma unroll
+        for (int i = 0; i < kG; ++i) {
+          if (g + i < n) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+              n2 = fmaf(kf[i][c].x, kf[i][c].x,
+                        fmaf(kf[i][c].y, kf[i][c].y, fmaf(kf[i][c].z, kf[i][c].z, fmaf(kf[i][c].w, kf[i][c].w, n2))));
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(to_op8(kf[i]), aq[g + i], acc, 0, 0, 0);
+          }
+        }
+      }
+      norm[buf][wave][lane] = n2;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[buf][wave][r][lane] = acc[r];
+    // The buffer is written again two blocks on, after the next block's
+    // barrier, which the wave reading it here reaches only when it is done.
+    __syncthreads();
+    if (wave == (it & (kFewWaves - 1))) {
+      float m1 = -INFINITY, m2 = -INFINITY;
+      int i1 = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float t = part[buf][0][r][lane];
+#pragma unroll
+        for (int w = 1; w < kFewWaves; ++w) t += part[buf][w][r][lane];
+        const int row = 8 * (r >> 2) + 4 * half + (r & 3);
+        block_top2(kb * kKB + row < p.M ? t * kUnscale : -INFINITY, row, m1, m2, i1);
+      }
+      store_summary(p, r32, half, kb, m1, m2, i1);
+      if constexpr (!PREP) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) v += norm[buf][w][lane];
+        v += xor_shfl(v, 32);
+        const int64_t key = kb * kKB + r32;
+        if (half == 0 && key < p.M) p.rownorm2[key] = v;
+        float mx = key < p.M ? v : 0.f;
+#pragma unroll
+        for (int m = 1; m < 32; m <<= 1) mx = fmaxf(mx, xor_shfl(mx, m));
+        if (lane == 0) p.blocknorm2[kb] = mx;
+      }
+    }
+  }
+}
+
 // the rank order: larger score first, then lower index
 // Prepared index, operands: entry ((kb * nks + ks) * 2 + h) * 32 + r' holds
 // features [16 ks + 8 h, 16 ks + 8 h + 8) of key 32 kb + r as fp16(2^8 k)
@@ -417,7 +546,24 @@ static void error_bound_constants(RetrieveParams& p) {
 
 hipError_t launch_retrieve_screen(RetrieveParams& p, hipStream_t s) {
   error_bound_constants(p);
-  if (p.nkb > 0) {
+  if (p.nkb > 0 && p.Q <= kFewQ && p.E <= kFewMaxE) {
+    // Blocks per workgroup such that about five workgroups per CU share them
+    // evenly.
+    const int64_t each = (p.nkb + 1279) / 1280;
+    const dim3 grid(static_cast<unsigned>((p.nkb + each - 1) / each));
+    const dim3 block(64 * kFewWaves);
+    const bool prep = p.kop != nullptr;
+    if (p.nks <= 2 * kFewWaves) {
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 2>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 2>), grid, block, 0, s, p);
+    } else if (p.nks <= 8 * kFewWaves) {
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 8>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 8>), grid, block, 0, s, p);
+    } else {
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 16>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 16>), grid, block, 0, s, p);
+    }
+  } else if (p.nkb > 0) {
     const int64_t entries = static_cast<int64_t>(p.nqg) * p.nks * 64;
     hipLaunchKernelGGL(prep_kernel, dim3(static_cast<unsigned>((entries + 255) / 256)), dim3(256), 0, s, p);
     const int64_t nqwg = (p.Q + 32 * kRetWaves - 1) / (32 * kRetWaves);
