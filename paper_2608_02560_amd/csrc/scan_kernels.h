@@ -389,6 +389,146 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src, __builtin_bit_cast(int, v)));
 }
 
+// B_t[n] dt_t x_t on the matrix core, for 16-bit inputs with 16 states per
+// lane and no readout (summary and state-only kinds).  Both factors of
+// u = dt x have 8 significant bits, so u has at most 16 and splits exactly
+// into two bf16 halves u = hi + lo (hi truncated), and B hi, B lo and their
+// sum (24 bits) are exact in fp32: the product that leaves the matrix core is
+// the one a v_mul_f32 would give, bit for bit (halves below the smallest
+// normal, |u| < 2^-110, are dropped: at most 2^-126 |B|, the size of the
+// decays' own flushing).
+// v_mfma_f32_32x32x16_bf16 gives lane l, in registers 0..15, sixteen of the
+// 32 rows of column l mod 32 (the rows with bit 2 equal to l / 32), and takes
+// eight k slots of its column from lane l mod 32 and eight from lane
+// l mod 32 + 32.  So with its own (hi, lo) in the u operand, and a B operand
+// whose rows of lane half g are zero outside that half's slots, a lane gets
+// B[n] u of its own channel for its own 16 states: one instruction in place
+// of 16 multiplications and their DPP broadcasts or coefficient reads, for 3
+// (P = 1) or 4 instructions that split and pack u.  A slot pair (one dword)
+// carries one token (P = 1: four tokens share a u operand) or, for P > 1, one
+// of the two state groups that lanes 0-15 and 16-31 of a half hold.
+// These kinds are bound by vector issue: 69 instructions a token before, 57
+// now and one matrix instruction, which takes 20-30 cycles of it (16 output
+// registers).  Long context (2 x 65,536 x 2048, both passes) 1442 -> 1311
+// us, N = 64 states (96 x 3000 x 1536) 3925 -> 3705 us.  With a readout the
+// gain is 2-3% at two waves per SIMD and the registers for C_t beside the
+// products cost the four-wave launches a wave (query prefill 43 -> 54 us), so
+// that kind keeps its multiplications, and so does the one-call query kernel,
+// whose decision needs the LDS.
+// Zero times infinity would spread over tokens and channels here: a tile with
+// a non-finite u or B takes the multiplications instead (mx_finite).
+typedef float mx_float16 __attribute__((ext_vector_type(16)));
+typedef __bf16 mx_bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t mx_u32x4 __attribute__((ext_vector_type(4)));
+
+// Wave-private LDS of a tile of T tokens: the B operand rows (one 16-byte
+// slot set per token and state, of which only the token's own dwords are ever
+// written) and a zero row for the other half's rows.
+template <int N, int T>
+struct MxLds {
+  static constexpr int kRows = N == 64 ? 32 : 16;  // the lane halves' states differ for N = 64 only
+  uint32_t a[T][kRows + 1][4];                     // row kRows: zeros
+};
+
+// Dword of token k's slot pair for state group grp (of a lane or a row).
+template <int N>
+__device__ __forceinline__ int mx_slot(int k, int grp) {
+  return N == 16 ? k & 3 : 2 * (k & 1) + (grp & 1);
+}
+
+// B_t of a tile in registers: the T rows are T N / 2 consecutive dwords of
+// two coefficients, dword l (+ 64 i) in lane l.
+template <int N, int T>
+struct MxTile {
+  static constexpr int kDw = T * N / 2;
+  static constexpr int kLoads = (kDw + 63) / 64;
+  uint32_t b[kLoads];
+
+  // `bytes`: the range of `rb`.  Dwords of tokens past the chunk lie past it
+  // and read as zero; the offset stops at its end, where every lane's does.
+  __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t rb, uint32_t bytes, int tile) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t at = static_cast<uint32_t>(tile) * (kDw * 4u);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      b[i] = __builtin_amdgcn_raw_buffer_load_b32(
+          rb, 64 * i + lane < kDw ? 4u * (64 * i + lane) : kDropOffset, at < bytes ? at : bytes, 0);
+  }
+
+  // The tile into the wave's LDS slice.  Written as bytes, so the compiler
+  // keeps the order with the operand reads (a wave's LDS accesses complete in
+  // order).  Returns the largest magnitude of this lane's B; NaN if one is
+  // NaN or infinite (an infinity twice in a dword is a NaN).
+  __device__ __forceinline__ float stage(MxLds<N, T>& s) const {
+    const int lane = threadIdx.x & 63;
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int dw = 64 * i + lane;
+      const uint32_t d0 = __builtin_amdgcn_perm(b[i], b[i], 0x01000100u);  // low half twice
+      const uint32_t d1 = __builtin_amdgcn_perm(b[i], b[i], 0x03020302u);  // high half twice
+      m = __builtin_elementwise_maximum(m, fabsf(__uint_as_float(d0)));
+      m = __builtin_elementwise_maximum(m, fabsf(__uint_as_float(d1)));
+      if (kDw % 64 == 0 || dw < kDw) {
+        const int k = dw / (N / 2);        // token of the tile
+        const int j = 2 * (dw % (N / 2));  // first coefficient
+        const int slot = mx_slot<N>(k, j / 16);
+        const int row = N == 64 ? 16 * (j / 32) + (j & 15) : j & 15;
+        __builtin_memcpy(reinterpret_cast<char*>(&s.a[k][row][slot]), &d0, 4);
+        __builtin_memcpy(reinterpret_cast<char*>(&s.a[k][row + 1][slot]), &d1, 4);
+      }
+    }
+    return m;
+  }
+};
+
+// Zeroes a slice (once, before its first tile).
+template <int N, int T>
+__device__ __forceinline__ void mx_clear(MxLds<N, T>& s) {
+  uint32_t* w = &s.a[0][0][0];
+  for (int i = threadIdx.x & 63; i < static_cast<int>(sizeof(s) / 4); i += 64) w[i] = 0;
+}
+
+// This lane's operand row within a token's rows (the zero row where the row
+// belongs to the other lane half).
+template <int N>
+__device__ __forceinline__ int mx_row() {
+  const int lane = threadIdx.x & 63;
+  const int r = lane & 31, g = lane >> 5;
+  const int n = 4 * (r >> 3) + (r & 3) + (N == 64 ? 16 * g : 0);
+  return ((r >> 2) & 1) == g ? n : (N == 64 ? 32 : 16);
+}
+
+// B_t u for this lane's 16 states: `row`, this lane's operand row of the
+// token; `u`, the (hi, lo) pairs of the tokens that share the operand.
+__device__ __forceinline__ mx_float16 mx_product(const uint32_t (&row)[4], const mx_u32x4& u) {
+  const mx_u32x4 a = *reinterpret_cast<const mx_u32x4*>(row);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(mx_bf16x8, a),
+                                                 __builtin_bit_cast(mx_bf16x8, u), mx_float16{}, 0, 0, 0);
+}
+
+// Puts token k's u into the operand as its two bf16 halves (hi, truncated,
+// in the low half of the dword, lo in the high half).  For P > 1 the token's
+// other dword is zero: sel[0], sel[1] are the byte selections of this lane's
+// two dwords, one the packing and one four zero bytes.
+constexpr uint32_t kMxPack = 0x07060302u, kMxZero = 0x0c0c0c0cu;
+template <int P>
+__device__ __forceinline__ void mx_put(mx_u32x4& f, int k, float u, const uint32_t (&sel)[2]) {
+  const float lo = u - __uint_as_float(__float_as_uint(u) & 0xffff0000u);
+  const uint32_t ub = __float_as_uint(u), lb = __float_as_uint(lo);
+  if constexpr (P == 1) {
+    f[k & 3] = __builtin_amdgcn_perm(lb, ub, kMxPack);
+  } else {
+    f[2 * (k & 1)] = __builtin_amdgcn_perm(lb, ub, sel[0]);
+    f[2 * (k & 1) + 1] = __builtin_amdgcn_perm(lb, ub, sel[1]);
+  }
+}
+
+// Every lane's m finite (all lanes active; wave-uniform).
+__device__ __forceinline__ bool mx_finite(float m) {
+  return __builtin_amdgcn_ballot_w64(!(m < INFINITY)) == 0;
+}
+
 // One lane = one (b, d) channel over one time chunk.  HASZ: gate present.
 //   KIND == kReadout:   y and (last chunk) hT
 //   KIND == kStateOnly: hT only (y == NULL: C, z, Dskip unread)
@@ -525,12 +665,12 @@ __device__ __forceinline__ void scan_body(
   // and the readout use plain VALU operands instead of DPP broadcasts.  The
   // slice is private to the wave: no barrier.
   // Used where it was measured to pay: with a readout (32 broadcasts per
-  // token replaced), when a channel spans several lanes (N > 16), and for
-  // readout-free N = 16 scans over 16-bit inputs in 4-token tiles, whose
-  // staging is one dword per lane (the long-context summary pass: 2.67 ->
-  // 2.64 ms); with per-token staging a readout-free N = 16 scan saves only
-  // the 16 B broadcasts, less than the staging costs.
-  constexpr bool kLds = NL == 16 && (kRead || P > 1 || (sizeof(typename SI::raw) == 2 && kPF == 4));
+  // token replaced) and when a channel spans several lanes (N > 16)
+  // (a readout-free N = 16 scan saves only the 16 B broadcasts, less than the
+  // staging costs).  Readout-free scans over 16-bit inputs take B_t u from the
+  // matrix core instead (kMx, MxTile above).
+  constexpr bool kMx = NL == 16 && sizeof(typename SI::raw) == 2 && !kRead && !DEC;
+  constexpr bool kLds = NL == 16 && !kMx && (kRead || P > 1);
   // 16-bit coefficients with N = 16 in one lane: a 4-token tile's B (and C)
   // rows are 4 x 16 x 2 bytes = 32 dwords, so lanes 0..31 fetch one dword
   // each (token l / 8, coefficients 2 (l mod 8) and 2 (l mod 8) + 1): one
@@ -551,6 +691,19 @@ __device__ __forceinline__ void scan_body(
     uint32_t bw, cw;  // kBcWord: this lane's dword of the tile's B / C rows
   };
   Tile t0b, t1b;
+  // kMx: B_t two tiles ahead in registers (even and odd tiles), one tile ahead
+  // in LDS, so that a tile's operand reads never wait for its staging (long
+  // context 1409 -> 1322 us)
+  MxTile<kMx ? N : 16, kPF> b_even, b_odd;
+  float b_max = 0.f;  // largest |B| this lane staged of the current tile
+  __shared__ __attribute__((aligned(16))) MxLds<kMx ? N : 16, kMx ? kPF : 1> mx_lds[kMx ? kSWaves : 1][2];
+  auto& mx = mx_lds[kMx ? wave : 0];
+  const int mxr = kMx ? mx_row<N>() : 0;
+  const uint32_t mxsel[2] = {(grp & 1) == 0 ? kMxPack : kMxZero, (grp & 1) == 0 ? kMxZero : kMxPack};
+  if constexpr (kMx) {
+    mx_clear(mx[0]);
+    mx_clear(mx[1]);
+  }
 
   __shared__ __attribute__((aligned(16))) float bc_lds[kLds ? kSBlock / 64 : 1][kLds ? kPF : 1][2][kLds ? N : 1];
   // bf16 coefficients go in as raw bits into the high half of a word whose
@@ -619,7 +772,7 @@ __device__ __forceinline__ void scan_body(
       tb.x[k] = SI::load(rx, dl, so);
       tb.dt[k] = SI::load(rd, dl, so);
       if constexpr (HASZ) tb.z[k] = SI::load(rz, dl, so);
-      if constexpr (!kBcWord) {
+      if constexpr (!kBcWord && !kMx) {
         const uint32_t sb = static_cast<uint32_t>(st) * bc_row;
 #pragma unroll
         for (int j = 0; j < G; ++j) {
@@ -662,12 +815,17 @@ __device__ __forceinline__ void scan_body(
   __shared__ __attribute__((aligned(16))) st_half8 traj_lds[kTrajT ? kSBlock / 64 : 1][kTrajT ? 128 : 1];
   const int nlive = static_cast<int>(D - wave_d0 < 64 ? D - wave_d0 : 64);  // live channels of the wave
   float dtacc = 0.f;
-  auto step = [&](const Tile& tb, int k, int st) {
+  // Token k of the tile, token st of the chunk; bu: B_t u of this lane's
+  // states (kMx only).
+  auto step = [&](const Tile& tb, int k, int st, const mx_float16& bu) {
     const float xv = SI::f32(tb.x[k]);
     const float dtv = SI::f32(tb.dt[k]);
     const float u = dtv * xv;
     float acc = 0.f;
-    if constexpr (kLds) {
+    if constexpr (kMx) {
+#pragma unroll
+      for (int n = 0; n < NL; ++n) h[n] = fmaf(__builtin_amdgcn_exp2f(dtv * a2[n]), h[n], bu[n]);
+    } else if constexpr (kLds) {
       Coef cf;
       read_coef(cf, k);
       token_vgpr<NL, kRead>(h, a2, dtv, u, cf.b, cf.c, acc, std::make_integer_sequence<int, 16>{});
@@ -719,17 +877,64 @@ __device__ __forceinline__ void scan_body(
   // The balance step runs at the head of each iteration of the time loop
   // (every 2 tiles), which is a block boundary anyway, so the unrolled body
   // stays one straight-line block whether or not the launch balances.
-  auto run_tile = [&](const Tile& tb, int tile) {
-    stage(tb);
+  // Tile `tile` (GUARD: of which only tokens before nsteps run).  ODD: its
+  // parity, which names its buffers.
+  auto run_tile = [&](const Tile& tb, int tile, auto guard, auto odd) {
+    constexpr bool kGuard = decltype(guard)::value;
+    constexpr int kOdd = decltype(odd)::value;
+    if constexpr (kMx) {
+      const auto& now = mx[kOdd];
+      float m = b_max;
+      b_max = (kOdd ? b_even : b_odd).stage(mx[1 - kOdd]);
+      (kOdd ? b_even : b_odd).fetch(rb, ns * bc_row, tile + 3);
+      constexpr int kShare = P == 1 ? 4 : 2;  // tokens of one u operand
+      mx_u32x4 uf[kPF / kShare];
 #pragma unroll
-    for (int k = 0; k < kPF; ++k) step(tb, k, tile * kPF + k);
-  };
-  auto run_tile_guarded = [&](const Tile& tb, int tile) {
-    stage(tb);
+      for (int k = 0; k < kPF; ++k) {
+        const float u = SI::f32(tb.dt[k]) * SI::f32(tb.x[k]);
+        mx_put<P>(uf[k / kShare], k, u, mxsel);
+        m = __builtin_elementwise_maximum(m, fabsf(u));
+      }
+      if (mx_finite(m)) {
 #pragma unroll
-    for (int k = 0; k < kPF; ++k)
-      if (tile * kPF + k < nsteps) step(tb, k, tile * kPF + k);
+        for (int k = 0; k < kPF; ++k) {
+          if (kGuard && tile * kPF + k >= nsteps) break;
+          step(tb, k, tile * kPF + k, mx_product(now.a[k][mxr], uf[k / kShare]));
+        }
+      } else {
+        // one token per round, so this path needs few registers
+#pragma unroll 1
+        for (int k = 0; k < kPF; ++k) {
+          if (kGuard && tile * kPF + k >= nsteps) break;
+          Tile tc;
+          tc.x[0] = tb.x[0];
+          tc.dt[0] = tb.dt[0];
+#pragma unroll
+          for (int i = 1; i < kPF; ++i) {
+            tc.x[0] = k == i ? tb.x[i] : tc.x[0];
+            tc.dt[0] = k == i ? tb.dt[i] : tc.dt[0];
+          }
+          const float u = SI::f32(tc.dt[0]) * SI::f32(tc.x[0]);
+          mx_float16 bu;
+#pragma unroll
+          for (int n = 0; n < NL; ++n) {
+            const uint32_t w = now.a[k][N == 64 ? 16 * (grp >> 1) + n : n][mx_slot<N>(k, grp)];
+            bu[n] = u * __uint_as_float(w & 0xffff0000u);
+          }
+          step(tc, 0, tile * kPF + k, bu);
+        }
+      }
+    } else {
+      stage(tb);
+#pragma unroll
+      for (int k = 0; k < kPF; ++k)
+        if (!kGuard || tile * kPF + k < nsteps) step(tb, k, tile * kPF + k, mx_float16{});
+    }
   };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  constexpr std::false_type whole{};
+  constexpr std::true_type guarded{};
 
   if constexpr (DEC) {
     // Wave 0 decides while the others wait; then every wave requests its
@@ -755,20 +960,28 @@ __device__ __forceinline__ void scan_body(
     // Tile 0 completes before tile 1 is requested (vmcnt(0); lgkmcnt and
     // expcnt untouched): at launch every wave requests at once, and tile 0
     // then does not queue behind tile 1 (corpus encode 1.2445 -> 1.2297 ms).
+    if constexpr (kMx) {
+      b_even.fetch(rb, ns * bc_row, 0);
+      b_odd.fetch(rb, ns * bc_row, 1);
+    }
     __builtin_amdgcn_s_waitcnt(0x0F70);
+    if constexpr (kMx) {
+      b_max = b_even.stage(mx[0]);
+      b_even.fetch(rb, ns * bc_row, 2);
+    }
     int tile = 0;
     // Pairs of whole tiles: straight-line code, no per-token guards.
     for (; (tile + 2) * kPF <= nsteps; tile += 2) {
       if (fair) balance_step(progress, wave, tile);
       fetch(t1b, tile + 1);
-      run_tile(t0b, tile);
+      run_tile(t0b, tile, whole, even);
       fetch(t0b, tile + 2);
-      run_tile(t1b, tile + 1);
+      run_tile(t1b, tile + 1, whole, odd);
     }
     // Fewer than 2 kPF tokens remain: tile `tile` is in t0b.
     fetch(t1b, tile + 1);
-    run_tile_guarded(t0b, tile);
-    run_tile_guarded(t1b, tile + 1);
+    run_tile(t0b, tile, guarded, even);
+    run_tile(t1b, tile + 1, guarded, odd);
   }
 
   if (!live) return;
@@ -781,15 +994,15 @@ __device__ __forceinline__ void scan_body(
   }
 }
 
-// The readout-free kinds over 16-bit inputs with N = 16 (the chunked scan's
-// summary pass, state-only encodes) are built for at most 128 VGPRs: four
-// waves per SIMD, two 512-thread workgroups per CU.  Left to itself the
-// compiler gave them 135-138, one workgroup per CU (two waves per SIMD) in
-// the many-round launches of the summary pass; at 128 it keeps a few values
-// that live across the time loop in scratch, none inside it.  Every other
-// instantiation keeps the compiler's own allocation.
+// The readout-free kinds over 16-bit inputs with 16 states per lane (the
+// chunked scan's summary pass, state-only encodes) are built for at most 128
+// VGPRs: four waves per SIMD, two 512-thread workgroups per CU, in launches of
+// many rounds; the few values this sends to scratch live across the time
+// loop, none inside it.  Trajectory capture keeps the compiler's allocation
+// (159; at 128 it spills inside the loop, 178 -> 285 us at every = 1), as
+// does every other instantiation.
 template <int N, typename TIn, int KIND, int TRAJ>
-constexpr int kScanMinWaves = (KIND != kReadout && TRAJ == 0 && N == 16 && sizeof(TIn) == 2) ? 4 : 1;
+constexpr int kScanMinWaves = (KIND != kReadout && TRAJ == 0 && N >= 16 && sizeof(TIn) == 2) ? 4 : 1;
 
 template <int N, typename TIn, typename TOut, typename TSt, int KIND, bool HASZ, int TRAJ>
 __global__ __launch_bounds__(kSBlock)
