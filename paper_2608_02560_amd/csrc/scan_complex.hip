@@ -6,12 +6,26 @@
 // stored interleaved.
 //
 // Same work decomposition as the real scan (one lane per (b, d) channel, 64
-// adjacent channels per wave, buffer loads, B_t / C_t reaching every lane as
-// DPP row_newbcast operands).  Per (t, d, n): exp2 of dt a' for the
-// magnitude; the angle dt w / (2 pi) in revolutions, reduced to [0, 1) by
-// v_fract_f32, then v_cos_f32 / v_sin_f32 (which take revolutions); then the
-// complex multiply-add
+// adjacent channels per wave, buffer loads, 4-token tiles, for N = 16 the
+// tile's B_t / C_t through a wave-private LDS slice).  Per (t, d, n): exp2 of
+// dt a' for the magnitude; the angle dt w / (2 pi) in revolutions for v_cos_f32
+// / v_sin_f32; then the complex multiply-add
 //   re' = c re + s im + B u,   im' = c im - s re,   (c, s) = |decay| (cos, sin).
+// The two take angles of up to 256 revolutions either way and reduce them
+// exactly: over 4 M angles in each of [0, 8], [0, 64] and [0, 256) and their
+// negatives the results are as close to the fp64 ones as those of angles
+// reduced by v_fract_f32 first (largest error 1.25e-7 both; closer for negative
+// angles below one revolution, 1.2e-7 against 3.6e-7, where fract rounds).  So
+// a tile whose |dt| max |w| stays below that skips the 16 reductions a token;
+// other tiles reduce.
+// The kernel is bound by vector issue (11 plain instructions and 3
+// transcendentals per state and token before, 10 and 3 now, two of them no
+// longer DPP forms).  8 x 3000 x 2048 bf16, both passes 730 -> 665 us (702 with
+// the LDS coefficients alone); 64 x 1000 x 2048 977 -> 893; states only, 128 x
+// 500 x 2048 881 -> 814; fp32 64 x 500 x 2048 486 -> 445.  One wave fewer per
+// SIMD fits in readout launches of many rounds (two of at most two): 256 x 200
+// x 2048 stays at 795 us.  At most 168 VGPRs sends values to scratch inside the
+// loop (721 us).
 //
 // Long sequences over few channels are cut into time chunks as in the real
 // scan (two levels):
@@ -30,19 +44,24 @@ namespace {
 
 constexpr float kInv2Pi = 0.15915494309189535f;
 
-template <int N, int... m>
+// One state's update; bu = B_t u.  REDUCE: the angle may leave the domain of
+// v_cos_f32 / v_sin_f32 (256 revolutions either way) and is reduced first.
+template <bool REDUCE>
+__device__ __forceinline__ void cstate(float& hr, float& hi, float a2, float w1, float dtv, float bu) {
+  const float mag = __builtin_amdgcn_exp2f(dtv * a2);
+  const float rev = REDUCE ? __builtin_amdgcn_fractf(dtv * w1) : dtv * w1;
+  const float c = mag * __builtin_amdgcn_cosf(rev);
+  const float s = mag * __builtin_amdgcn_sinf(rev);
+  const float re = hr;
+  hr = fmaf(c, re, fmaf(s, hi, bu));
+  hi = fmaf(c, hi, -(s * re));
+}
+
+template <bool REDUCE, int N, int... m>
 __device__ __forceinline__ void ctoken(float (&hr)[N], float (&hi)[N], const float (&a2)[N],
                                        const float (&w1)[N], float dtv, float u, float bv,
                                        std::integer_sequence<int, m...>) {
-  ((void)[&] {
-    const float mag = __builtin_amdgcn_exp2f(dtv * a2[m]);
-    const float rev = __builtin_amdgcn_fractf(dtv * w1[m]);
-    const float c = mag * __builtin_amdgcn_cosf(rev);
-    const float s = mag * __builtin_amdgcn_sinf(rev);
-    const float re = hr[m];
-    hr[m] = fmaf(c, re, fmaf(s, hi[m], u * row_bcast<m>(bv)));
-    hi[m] = fmaf(c, hi[m], -(s * re));
-  }(), ...);
+  (cstate<REDUCE>(hr[m], hi[m], a2[m], w1[m], dtv, u * row_bcast<m>(bv)), ...);
 }
 
 template <int N, typename TSt>
@@ -142,34 +161,92 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
   const int lane16 = lane & 15;
   const uint32_t el = static_cast<uint32_t>(lane16 < N ? lane16 : N - 1) * sizeof(TIn);
 
+  // N = 16: the B (and C) rows of a tile are 32 (16-bit inputs) or 64
+  // consecutive dwords, dword l in lane l.  They go as fp32 into a
+  // wave-private LDS slice when the tile is consumed and come back as
+  // same-address 16-byte reads, as in the real scan: plain operands in place
+  // of 32 DPP broadcasts a token, which issue more slowly, and one load per
+  // array and tile in place of four.  State-only kinds gain too (without it
+  // 8 x 3000 x 2048 643 us, with it 626).  Shorter N keep the broadcasts.
+  constexpr bool kLds = N == 16;
+  constexpr int kDw = kPFPlain * N * static_cast<int>(sizeof(TIn)) / 4;
+  __shared__ __attribute__((aligned(16))) float bc_lds[kLds ? kSWaves : 1][kLds ? kPFPlain : 1][2][kLds ? N : 1];
+
   struct Tile {
-    typename SI::raw x[kPFWide], dt[kPFWide], z[kPFWide], b[kPFWide], c[kPFWide];
+    typename SI::raw x[kPFPlain], dt[kPFPlain], z[kPFPlain], b[kPFPlain], c[kPFPlain];
+    uint32_t bw, cw;  // kLds: this lane's dword of the tile's B / C rows
   };
   Tile t0b, t1b;
   const int last = nsteps > 0 ? nsteps - 1 : 0;
   auto fetch = [&](Tile& tb, int tile) {
+    if constexpr (kLds) {
+      // dwords of tokens past the chunk lie past the range and read as zero
+      const uint32_t end = ns * bc_row;
+      const uint32_t at = static_cast<uint32_t>(tile) * (kDw * 4u);
+      const uint32_t off = lane < kDw ? 4u * static_cast<uint32_t>(lane) : kDropOffset;
+      tb.bw = __builtin_amdgcn_raw_buffer_load_b32(rb, off, at < end ? at : end, 0);
+      if constexpr (kRead) tb.cw = __builtin_amdgcn_raw_buffer_load_b32(rc, off, at < end ? at : end, 0);
+    }
 #pragma unroll
-    for (int k = 0; k < kPFWide; ++k) {
-      int st = tile * kPFWide + k;
+    for (int k = 0; k < kPFPlain; ++k) {
+      int st = tile * kPFPlain + k;
       st = st < last ? st : last;
       const uint32_t so = static_cast<uint32_t>(st) * in_row;
       tb.x[k] = SI::load(rx, dl, so);
       tb.dt[k] = SI::load(rd, dl, so);
       if constexpr (HASZ) tb.z[k] = SI::load(rz, dl, so);
-      const uint32_t sb = static_cast<uint32_t>(st) * bc_row;
-      tb.b[k] = SI::load(rb, el, sb);
-      if constexpr (kRead) tb.c[k] = SI::load(rc, el, sb);
+      if constexpr (!kLds) {
+        const uint32_t sb = static_cast<uint32_t>(st) * bc_row;
+        tb.b[k] = SI::load(rb, el, sb);
+        if constexpr (kRead) tb.c[k] = SI::load(rc, el, sb);
+      }
     }
   };
+  auto put = [&](int which, uint32_t w) {
+    if constexpr (sizeof(TIn) == 2) {  // token l / 8, coefficients 2 (l mod 8) and the next
+      float* dst = &bc_lds[wave][lane >> 3][which][2 * (lane & 7)];
+      dst[0] = __uint_as_float(w << 16);
+      dst[1] = __uint_as_float(w & 0xffff0000u);
+    } else {
+      bc_lds[wave][lane >> 4][which][lane & 15] = __uint_as_float(w);
+    }
+  };
+  auto stage = [&](const Tile& tb) {
+    if constexpr (kLds) {
+      if (lane < kDw) {
+        put(0, tb.bw);
+        if constexpr (kRead) put(1, tb.cw);
+      }
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the writes are done before any read
+    }
+  };
+
   float dtacc = 0.f;
-  auto step = [&](const Tile& tb, int k, int st) {
+  // Token k of the tile (its registers) and of the staged coefficients (kc),
+  // token st of the chunk.
+  auto step = [&](const Tile& tb, int k, int kc, int st, auto reduce) {
+    constexpr bool kReduce = decltype(reduce)::value;
     const float xv = SI::f32(tb.x[k]);
     const float dtv = SI::f32(tb.dt[k]);
     const float u = dtv * xv;
-    ctoken<N>(hr, hi, a2, w1, dtv, u, SI::f32(tb.b[k]), std::make_integer_sequence<int, kPer>{});
+    float acc = 0.f;
+    if constexpr (kLds) {
+      float bl[N], cl[N];
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        bl[n] = bc_lds[wave][kc][0][n];
+        cl[n] = kRead ? bc_lds[wave][kc][1][n] : 0.f;
+      }
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        cstate<kReduce>(hr[n], hi[n], a2[n], w1[n], dtv, u * bl[n]);
+        if constexpr (kRead) acc = fmaf(cl[n], hr[n], acc);
+      }
+    } else {
+      ctoken<kReduce>(hr, hi, a2, w1, dtv, u, SI::f32(tb.b[k]), std::make_integer_sequence<int, kPer>{});
+      if constexpr (kRead) readout_group<N, 0>(acc, SI::f32(tb.c[k]), hr);
+    }
     if constexpr (kRead) {
-      float acc = 0.f;
-      readout_group<N, 0>(acc, SI::f32(tb.c[k]), hr);
       float out = fmaf(dsk, xv, acc);
       if constexpr (HASZ) {
         const float zv = SI::f32(tb.z[k]);
@@ -180,30 +257,69 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
     }
     if constexpr (KIND == kSummary) dtacc += dtv;
   };
-  auto run_tile = [&](const Tile& tb, int tile) {
+  // Largest |w / (2 pi)| of this lane's states (NaN if one is).  Rounding is
+  // monotone, so |dt| w_max < 256 bounds every dt w of the tile.
+  float w_max = 0.f;
 #pragma unroll
-    for (int k = 0; k < kPFWide; ++k) step(tb, k, tile * kPFWide + k);
-  };
-  auto run_tile_guarded = [&](const Tile& tb, int tile) {
+  for (int n = 0; n < N; ++n) w_max = __builtin_elementwise_maximum(w_max, fabsf(w1[n]));
+  auto run_tile = [&](const Tile& tb, int tile, auto guard) {
+    constexpr bool kGuard = decltype(guard)::value;
+    stage(tb);
+    bool direct = false;
+    if constexpr (kLds) {
+      float m = 0.f;
 #pragma unroll
-    for (int k = 0; k < kPFWide; ++k)
-      if (tile * kPFWide + k < nsteps) step(tb, k, tile * kPFWide + k);
+      for (int k = 0; k < kPFPlain; ++k) m = __builtin_elementwise_maximum(m, fabsf(SI::f32(tb.dt[k])));
+      direct = __builtin_amdgcn_ballot_w64(!(m * w_max < 256.f)) == 0;
+    }
+    if (direct) {
+#pragma unroll
+      for (int k = 0; k < kPFPlain; ++k) {
+        if (kGuard && tile * kPFPlain + k >= nsteps) break;
+        step(tb, k, k, tile * kPFPlain + k, std::false_type{});
+      }
+    } else if constexpr (kLds) {
+      // one token per round, so this path needs little code and few registers
+#pragma unroll 1
+      for (int k = 0; k < kPFPlain; ++k) {
+        if (kGuard && tile * kPFPlain + k >= nsteps) break;
+        Tile tc;
+        tc.x[0] = tb.x[0];
+        tc.dt[0] = tb.dt[0];
+        if constexpr (HASZ) tc.z[0] = tb.z[0];
+#pragma unroll
+        for (int i = 1; i < kPFPlain; ++i) {
+          tc.x[0] = k == i ? tb.x[i] : tc.x[0];
+          tc.dt[0] = k == i ? tb.dt[i] : tc.dt[0];
+          if constexpr (HASZ) tc.z[0] = k == i ? tb.z[i] : tc.z[0];
+        }
+        step(tc, 0, k, tile * kPFPlain + k, std::true_type{});
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kPFPlain; ++k) {
+        if (kGuard && tile * kPFPlain + k >= nsteps) break;
+        step(tb, k, k, tile * kPFPlain + k, std::true_type{});
+      }
+    }
   };
+  constexpr std::false_type whole{};
+  constexpr std::true_type guarded{};
 
   if (nsteps > 0) {
     fetch(t0b, 0);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): tile 0 in before tile 1 is requested
     int tile = 0;
-    for (; (tile + 2) * kPFWide <= nsteps; tile += 2) {
+    for (; (tile + 2) * kPFPlain <= nsteps; tile += 2) {
       if (fair) balance_step(progress, wave, tile);
       fetch(t1b, tile + 1);
-      run_tile(t0b, tile);
+      run_tile(t0b, tile, whole);
       fetch(t0b, tile + 2);
-      run_tile(t1b, tile + 1);
+      run_tile(t1b, tile + 1, whole);
     }
     fetch(t1b, tile + 1);
-    run_tile_guarded(t0b, tile);
-    run_tile_guarded(t1b, tile + 1);
+    run_tile(t0b, tile, guarded);
+    run_tile(t1b, tile + 1, guarded);
   }
 
   if (!live) return;
