@@ -59,6 +59,13 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
   const int hi = __builtin_amdgcn_readlane(static_cast<int>(__double2hiint(v)), l);
   return __hiloint2double(hi, lo);
 }
+__device__ __forceinline__ double wave_max_d(double v) {
+  v = fmax(v, dpp_d<kQuadSwap1>(v));
+  v = fmax(v, dpp_d<kQuadSwap2>(v));
+  v = fmax(v, dpp_d<kRowRor4>(v));
+  v = fmax(v, dpp_d<kRowRor8>(v));
+  return fmax(fmax(readlane_d(v, 0), readlane_d(v, 16)), fmax(readlane_d(v, 32), readlane_d(v, 48)));
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
   v += dpp_d<kQuadSwap1>(v);
   v += dpp_d<kQuadSwap2>(v);
