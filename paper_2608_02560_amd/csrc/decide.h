@@ -89,7 +89,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// decide: one wave per query (the decision of the retrieval file's comment).  For the
+// decide: one wave, or NW waves, per query (the decision of the retrieval file's comment).  For the
 // k best keys the bound uses t_k, the k-th largest block maximum: k distinct
 // blocks hold a key with screen score >= t_k, so k keys have exact scores
 // >= t_k - e_max and every key of the exact top k has S~_i + e(i) >= that.

@@ -17,7 +17,7 @@
 //            32-key block) it keeps the largest screen score S~, its key, and
 //            the largest S~ of the block's other keys; and the squared norm
 //            of every key and the largest one of every block.
-//   decide   one wave per query: m = the largest screen score.  A key can
+//   decide   one wave per query (four for top-k and large indexes): m = the largest screen score.  A key can
 //            still be the fp64 maximum only if S~_i + e(i) >= m - e(i0), where
 //            e(i) = g |q| |k_i| + h (|q| + |k_i|) + tiny bounds the error of
 //            its screen score (g bounds the fp16 rounding and the fp32
