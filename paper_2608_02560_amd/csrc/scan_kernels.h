@@ -815,6 +815,32 @@ __device__ __forceinline__ void scan_body(
   __shared__ __attribute__((aligned(16))) st_half8 traj_lds[kTrajT ? kSBlock / 64 : 1][kTrajT ? 128 : 1];
   const int nlive = static_cast<int>(D - wave_d0 < 64 ? D - wave_d0 : 64);  // live channels of the wave
   float dtacc = 0.f;
+  // What follows the state update of a token: the sum of dt, a captured state.
+  auto finish = [&](float dtv) {
+    if constexpr (KIND == kSummary) dtacc += dtv;
+    if constexpr (TRAJ != 0) {
+      if (cd == 0) {  // wave-uniform
+        TSt* row = static_cast<TSt*>(p.traj) + (static_cast<int64_t>(b) * p.traj_count + slot) * D * N;
+        if constexpr (kTrajT) {
+          const st_float8 v0 = {h[0], h[1], h[2], h[3], h[4], h[5], h[6], h[7]};
+          const st_float8 v1 = {h[8], h[9], h[10], h[11], h[12], h[13], h[14], h[15]};
+          traj_lds[wave][2 * lane] = __builtin_convertvector(v0, st_half8);
+          traj_lds[wave][2 * lane + 1] = __builtin_convertvector(v1, st_half8);
+          const st_half8 o0 = traj_lds[wave][lane];
+          const st_half8 o1 = traj_lds[wave][64 + lane];
+          TSt* wrow = row + wave_d0 * N;
+          if ((lane >> 1) < nlive) *reinterpret_cast<st_half8*>(wrow + 8 * lane) = o0;
+          if (32 + (lane >> 1) < nlive) *reinterpret_cast<st_half8*>(wrow + 512 + 8 * lane) = o1;
+        } else if (live) {
+          store_state_vec<NL>(row + sofs, h);
+        }
+        ++slot;
+        cd = p.traj_every - 1;
+      } else {
+        --cd;
+      }
+    }
+  };
   // Token k of the tile, token st of the chunk; bu: B_t u of this lane's
   // states (kMx only).
   auto step = [&](const Tile& tb, int k, int st, const mx_float16& bu) {
@@ -850,29 +876,7 @@ __device__ __forceinline__ void scan_body(
       }
       SO::store(ry, dly, static_cast<uint32_t>(st) * out_row, out);
     }
-    if constexpr (KIND == kSummary) dtacc += dtv;
-    if constexpr (TRAJ != 0) {
-      if (cd == 0) {  // wave-uniform
-        TSt* row = static_cast<TSt*>(p.traj) + (static_cast<int64_t>(b) * p.traj_count + slot) * D * N;
-        if constexpr (kTrajT) {
-          const st_float8 v0 = {h[0], h[1], h[2], h[3], h[4], h[5], h[6], h[7]};
-          const st_float8 v1 = {h[8], h[9], h[10], h[11], h[12], h[13], h[14], h[15]};
-          traj_lds[wave][2 * lane] = __builtin_convertvector(v0, st_half8);
-          traj_lds[wave][2 * lane + 1] = __builtin_convertvector(v1, st_half8);
-          const st_half8 o0 = traj_lds[wave][lane];
-          const st_half8 o1 = traj_lds[wave][64 + lane];
-          TSt* wrow = row + wave_d0 * N;
-          if ((lane >> 1) < nlive) *reinterpret_cast<st_half8*>(wrow + 8 * lane) = o0;
-          if (32 + (lane >> 1) < nlive) *reinterpret_cast<st_half8*>(wrow + 512 + 8 * lane) = o1;
-        } else if (live) {
-          store_state_vec<NL>(row + sofs, h);
-        }
-        ++slot;
-        cd = p.traj_every - 1;
-      } else {
-        --cd;
-      }
-    }
+    finish(dtv);
   };
   // The balance step runs at the head of each iteration of the time loop
   // (every 2 tiles), which is a block boundary anyway, so the unrolled body
@@ -902,7 +906,12 @@ __device__ __forceinline__ void scan_body(
           step(tb, k, tile * kPF + k, mx_product(now.a[k][mxr], uf[k / kShare]));
         }
       } else {
-        // one token per round, so this path needs few registers
+        // One token per round and two states at a time: this path must not set
+        // the kernel's registers.  With all 16 products and exponentials at
+        // once it took 133-182 where the products' own path takes 105-159, and
+        // the readout-free kinds reloaded spilled addresses in every tile.
+        // N = 16 states 64 x 1000 x 2048, fp32 state 385 -> 280 us; trajectory
+        // of 64 states 256 x 200 x 1024, every 64th 505 -> 430 us.
 #pragma unroll 1
         for (int k = 0; k < kPF; ++k) {
           if (kGuard && tile * kPF + k >= nsteps) break;
@@ -914,14 +923,15 @@ __device__ __forceinline__ void scan_body(
             tc.x[0] = k == i ? tb.x[i] : tc.x[0];
             tc.dt[0] = k == i ? tb.dt[i] : tc.dt[0];
           }
-          const float u = SI::f32(tc.dt[0]) * SI::f32(tc.x[0]);
-          mx_float16 bu;
+          const float dtv = SI::f32(tc.dt[0]);
+          const float u = dtv * SI::f32(tc.x[0]);
+          const uint32_t* w0 = &now.a[k][N == 64 ? 16 * (grp >> 1) : 0][mx_slot<N>(k, grp)];
 #pragma unroll
           for (int n = 0; n < NL; ++n) {
-            const uint32_t w = now.a[k][N == 64 ? 16 * (grp >> 1) + n : n][mx_slot<N>(k, grp)];
-            bu[n] = u * __uint_as_float(w & 0xffff0000u);
+            h[n] = fmaf(__builtin_amdgcn_exp2f(dtv * a2[n]), h[n], u * __uint_as_float(w0[4 * n] & 0xffff0000u));
+            if (n % 2 == 1) __builtin_amdgcn_sched_barrier(0);
           }
-          step(tc, 0, tile * kPF + k, bu);
+          finish(dtv);
         }
       }
     } else {
@@ -997,10 +1007,9 @@ __device__ __forceinline__ void scan_body(
 // The readout-free kinds over 16-bit inputs with 16 states per lane (the
 // chunked scan's summary pass, state-only encodes) are built for at most 128
 // VGPRs: four waves per SIMD, two 512-thread workgroups per CU, in launches of
-// many rounds; the few values this sends to scratch live across the time
-// loop, none inside it.  Trajectory capture keeps the compiler's allocation
-// (159; at 128 it spills inside the loop, 178 -> 285 us at every = 1), as
-// does every other instantiation.
+// many rounds; they need 105-127, so nothing goes to scratch.  Trajectory
+// capture (123-159) and every other instantiation keep the compiler's
+// allocation.
 template <int N, typename TIn, int KIND, int TRAJ>
 constexpr int kScanMinWaves = (KIND != kReadout && TRAJ == 0 && N >= 16 && sizeof(TIn) == 2) ? 4 : 1;
 
