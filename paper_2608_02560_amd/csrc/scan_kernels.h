@@ -455,9 +455,8 @@ struct MxTile {
           rb, 64 * i + lane < kDw ? 4u * (64 * i + lane) : kDropOffset, at < bytes ? at : bytes, 0);
   }
 
-  // The tile into the wave's LDS slice.  Written as bytes, so the compiler
-  // keeps the order with the operand reads (a wave's LDS accesses complete in
-  // order).  Returns the largest magnitude of this lane's B; NaN if one is
+  // The tile into the wave's LDS slice (other lanes read it: wave_sync() lies
+  // between).  Returns the largest magnitude of this lane's B; NaN if one is
   // NaN or infinite (an infinity twice in a dword is a NaN).
   __device__ __forceinline__ float stage(MxLds<N, T>& s) const {
     const int lane = threadIdx.x & 63;
@@ -474,8 +473,8 @@ struct MxTile {
         const int j = 2 * (dw % (N / 2));  // first coefficient
         const int slot = mx_slot<N>(k, j / 16);
         const int row = N == 64 ? 16 * (j / 32) + (j & 15) : j & 15;
-        __builtin_memcpy(reinterpret_cast<char*>(&s.a[k][row][slot]), &d0, 4);
-        __builtin_memcpy(reinterpret_cast<char*>(&s.a[k][row + 1][slot]), &d1, 4);
+        s.a[k][row][slot] = d0;
+        s.a[k][row + 1][slot] = d1;
       }
     }
     return m;
@@ -888,6 +887,11 @@ __device__ __forceinline__ void scan_body(
     constexpr int kOdd = decltype(odd)::value;
     if constexpr (kMx) {
       const auto& now = mx[kOdd];
+      // The operands read here were staged a tile ago, and what is staged here
+      // was read a tile ago, each by other lanes of the wave: this keeps every
+      // LDS access on its side (no instruction; the LDS unit performs a wave's
+      // accesses in issue order).
+      wave_sync();
       float m = b_max;
       b_max = (kOdd ? b_even : b_odd).stage(mx[1 - kOdd]);
       (kOdd ? b_even : b_odd).fetch(rb, ns * bc_row, tile + 3);
@@ -976,6 +980,7 @@ __device__ __forceinline__ void scan_body(
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     if constexpr (kMx) {
+      wave_sync();  // the slices are cleared
       b_max = b_even.stage(mx[0]);
       b_even.fetch(rb, ns * bc_row, 2);
     }
