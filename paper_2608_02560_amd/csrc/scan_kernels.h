@@ -394,9 +394,8 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
 // u = dt x have 8 significant bits, so u has at most 16 and splits exactly
 // into two bf16 halves u = hi + lo (hi truncated), and B hi, B lo and their
 // sum (24 bits) are exact in fp32: the product that leaves the matrix core is
-// the one a v_mul_f32 would give, bit for bit (halves below the smallest
-// normal, |u| < 2^-110, are dropped: at most 2^-126 |B|, the size of the
-// decays' own flushing).
+// the one a v_mul_f32 would give, bit for bit, as long as u (below 2^-117 lo
+// loses bits) and B u (subnormal sums round more than once) are not too small.
 // v_mfma_f32_32x32x16_bf16 gives lane l, in registers 0..15, sixteen of the
 // 32 rows of column l mod 32 (the rows with bit 2 equal to l / 32), and takes
 // eight k slots of its column from lane l mod 32 and eight from lane
@@ -416,7 +415,11 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
 // that kind keeps its multiplications, and so does the one-call query kernel,
 // whose decision needs the LDS.
 // Zero times infinity would spread over tokens and channels here: a tile with
-// a non-finite u or B takes the multiplications instead (mx_finite).
+// a non-finite u or B takes the multiplications instead, and so does one with
+// a nonzero u or B below 2^-62 (MxRange), so that every result is the
+// multiplications'.  The test of the small ones takes 4 instructions a tile:
+// states of 96 x 1000 x 1536, N = 64, 1232 -> 1254 us; with zeros in
+// nearly every tile 1310 (x) to 1385 us (B).
 typedef float mx_float16 __attribute__((ext_vector_type(16)));
 typedef __bf16 mx_bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t mx_u32x4 __attribute__((ext_vector_type(4)));
@@ -436,8 +439,28 @@ __device__ __forceinline__ int mx_slot(int k, int grp) {
   return N == 16 ? k & 3 : 2 * (k & 1) + (grp & 1);
 }
 
+// Smallest and largest magnitude of a lane's operands (NaN if one is a NaN).
+constexpr float kMxLeast = 0x1p-62f;
+struct MxRange {
+  float least = INFINITY, most = 0.f;
+  __device__ __forceinline__ void add(float v) {
+    least = __builtin_elementwise_minimum(least, fabsf(v));
+    most = __builtin_elementwise_maximum(most, fabsf(v));
+  }
+  // The smallest again, of the values that are not zero.
+  __device__ __forceinline__ void add_nonzero(float v) {
+    least = __builtin_elementwise_minimum(least, v == 0.f ? INFINITY : fabsf(v));
+  }
+  // Every lane's operands finite and at least 2^-62: u keeps its bits, and no
+  // product is below 2^-124 (all lanes active; wave-uniform).
+  __device__ __forceinline__ bool inside() const {
+    return (__builtin_amdgcn_ballot_w64(!(least >= kMxLeast)) | __builtin_amdgcn_ballot_w64(!(most < INFINITY))) == 0;
+  }
+};
+
 // B_t of a tile in registers: the T rows are T N / 2 consecutive dwords of
-// two coefficients, dword l (+ 64 i) in lane l.
+// two coefficients, dword l (+ 64 i) in lane l (32 dwords: in lanes l and
+// l + 32, which then do the same).
 template <int N, int T>
 struct MxTile {
   static constexpr int kDw = T * N / 2;
@@ -452,32 +475,44 @@ struct MxTile {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i)
       b[i] = __builtin_amdgcn_raw_buffer_load_b32(
-          rb, 64 * i + lane < kDw ? 4u * (64 * i + lane) : kDropOffset, at < bytes ? at : bytes, 0);
+          rb, 4u * ((64 * i + lane) % kDw), at < bytes ? at : bytes, 0);
   }
 
   // The tile into the wave's LDS slice (other lanes read it: wave_sync() lies
-  // between).  Returns the largest magnitude of this lane's B; NaN if one is
-  // NaN or infinite (an infinity twice in a dword is a NaN).
-  __device__ __forceinline__ float stage(MxLds<N, T>& s) const {
-    const int lane = threadIdx.x & 63;
-    float m = 0.f;
+  // between).  Returns the range of this lane's B (an infinity twice in a
+  // dword is a NaN).
+  __device__ __forceinline__ MxRange stage(MxLds<N, T>& s) const {
+    MxRange r;
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const int dw = 64 * i + lane;
       const uint32_t d0 = __builtin_amdgcn_perm(b[i], b[i], 0x01000100u);  // low half twice
       const uint32_t d1 = __builtin_amdgcn_perm(b[i], b[i], 0x03020302u);  // high half twice
-      m = __builtin_elementwise_maximum(m, fabsf(__uint_as_float(d0)));
-      m = __builtin_elementwise_maximum(m, fabsf(__uint_as_float(d1)));
-      if (kDw % 64 == 0 || dw < kDw) {
-        const int k = dw / (N / 2);        // token of the tile
-        const int j = 2 * (dw % (N / 2));  // first coefficient
-        const int slot = mx_slot<N>(k, j / 16);
-        const int row = N == 64 ? 16 * (j / 32) + (j & 15) : j & 15;
-        s.a[k][row][slot] = d0;
-        s.a[k][row + 1][slot] = d1;
-      }
+      r.add(__uint_as_float(d0));
+      r.add(__uint_as_float(d1));
+      uint32_t* w = at(s, i);
+      w[0] = d0;
+      w[4] = d1;
     }
-    return m;
+    return r;
+  }
+
+  // Adds this lane's nonzero B of a staged tile.
+  static __device__ __forceinline__ void add_nonzero(MxRange& r, MxLds<N, T>& s) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const uint32_t* w = at(s, i);
+      r.add_nonzero(__uint_as_float(w[0] & 0xffff0000u));
+      r.add_nonzero(__uint_as_float(w[4] & 0xffff0000u));
+    }
+  }
+
+  // Where this lane's i-th dword goes: its first coefficient, the second one
+  // row (4 dwords) on.
+  static __device__ __forceinline__ uint32_t* at(MxLds<N, T>& s, int i) {
+    const int dw = (64 * i + (threadIdx.x & 63)) % kDw;
+    const int k = dw / (N / 2);        // token of the tile
+    const int j = 2 * (dw % (N / 2));  // first coefficient
+    return &s.a[k][N == 64 ? 16 * (j / 32) + (j & 15) : j & 15][mx_slot<N>(k, j / 16)];
   }
 };
 
@@ -521,11 +556,6 @@ __device__ __forceinline__ void mx_put(mx_u32x4& f, int k, float u, const uint32
     f[2 * (k & 1)] = __builtin_amdgcn_perm(lb, ub, sel[0]);
     f[2 * (k & 1) + 1] = __builtin_amdgcn_perm(lb, ub, sel[1]);
   }
-}
-
-// Every lane's m finite (all lanes active; wave-uniform).
-__device__ __forceinline__ bool mx_finite(float m) {
-  return __builtin_amdgcn_ballot_w64(!(m < INFINITY)) == 0;
 }
 
 // One lane = one (b, d) channel over one time chunk.  HASZ: gate present.
@@ -694,7 +724,7 @@ __device__ __forceinline__ void scan_body(
   // in LDS, so that a tile's operand reads never wait for its staging (long
   // context 1409 -> 1322 us)
   MxTile<kMx ? N : 16, kPF> b_even, b_odd;
-  float b_max = 0.f;  // largest |B| this lane staged of the current tile
+  MxRange b_range;  // of the B this lane staged of the current tile
   __shared__ __attribute__((aligned(16))) MxLds<kMx ? N : 16, kMx ? kPF : 1> mx_lds[kMx ? kSWaves : 1][2];
   auto& mx = mx_lds[kMx ? wave : 0];
   const int mxr = kMx ? mx_row<N>() : 0;
@@ -886,14 +916,15 @@ __device__ __forceinline__ void scan_body(
     constexpr bool kGuard = decltype(guard)::value;
     constexpr int kOdd = decltype(odd)::value;
     if constexpr (kMx) {
-      const auto& now = mx[kOdd];
+      auto& now = mx[kOdd];
       // The operands read here were staged a tile ago, and what is staged here
       // was read a tile ago, each by other lanes of the wave: this keeps every
       // LDS access on its side (no instruction; the LDS unit performs a wave's
       // accesses in issue order).
       wave_sync();
-      float m = b_max;
-      b_max = (kOdd ? b_even : b_odd).stage(mx[1 - kOdd]);
+      MxRange r = b_range;
+      const float b_least = r.least;
+      b_range = (kOdd ? b_even : b_odd).stage(mx[1 - kOdd]);
       (kOdd ? b_even : b_odd).fetch(rb, ns * bc_row, tile + 3);
       constexpr int kShare = P == 1 ? 4 : 2;  // tokens of one u operand
       mx_u32x4 uf[kPF / kShare];
@@ -901,9 +932,21 @@ __device__ __forceinline__ void scan_body(
       for (int k = 0; k < kPF; ++k) {
         const float u = SI::f32(tb.dt[k]) * SI::f32(tb.x[k]);
         mx_put<P>(uf[k / kShare], k, u, mxsel);
-        m = __builtin_elementwise_maximum(m, fabsf(u));
+        r.add(u);
       }
-      if (mx_finite(m)) {
+      bool exact = r.inside();
+      if (__builtin_expect(!exact, 0)) {
+        // perhaps zeros only, which are exact (coefficients past the chunk too)
+        r.least = b_least;
+        if (!r.inside()) {
+          r.least = INFINITY;
+          MxTile<kMx ? N : 16, kPF>::add_nonzero(r, now);
+        }
+#pragma unroll
+        for (int k = 0; k < kPF; ++k) r.add_nonzero(SI::f32(tb.dt[k]) * SI::f32(tb.x[k]));
+        exact = r.inside();
+      }
+      if (__builtin_expect(exact, 1)) {
 #pragma unroll
         for (int k = 0; k < kPF; ++k) {
           if (kGuard && tile * kPF + k >= nsteps) break;
@@ -981,7 +1024,7 @@ __device__ __forceinline__ void scan_body(
     __builtin_amdgcn_s_waitcnt(0x0F70);
     if constexpr (kMx) {
       wave_sync();  // the slices are cleared
-      b_max = b_even.stage(mx[0]);
+      b_range = b_even.stage(mx[0]);
       b_even.fetch(rb, ns * bc_row, 2);
     }
     int tile = 0;

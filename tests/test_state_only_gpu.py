@@ -83,7 +83,7 @@ def test_non_finite_inputs_stay_where_they_are(N, where, value):
 
 
 def test_products_near_the_smallest_normal():
-    """u below 2^-110: its low half may be flushed, at most 2^-126 |B| a token."""
+    """u below 2^-110, where bf16 halves of it end: within 2^-126 |B| a token."""
     B, L, D, N = 1, 40, 64, 16
     _, d = _inputs(B, L, D, N, seed=6)
     d["x"] = (d["x"].float() * 2.0 ** -112).to(torch.bfloat16)
@@ -94,3 +94,20 @@ def test_products_near_the_smallest_normal():
     d["x"] = (d["x"].float() * 2.0 ** 112).to(torch.bfloat16)
     h, ref = _both(d, L)
     assert torch.equal(h, ref) and np.isfinite(h.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("N", [16, 32, 64])
+@pytest.mark.parametrize("x,b", [(-112, 0), (-125, 0), (-133, 0), (-90, -50), (60, -130), (100, -128), (-64, -80)])
+def test_small_products_keep_their_bits(N, x, b):
+    """x and B scaled by powers of two until u = dt x, B or their product is
+    subnormal, every fifth x and every seventh B zero: the states equal the
+    multiplications' bit for bit."""
+    B, L, D = 2, 37, 136
+    _, d = _inputs(B, L, D, N, seed=60 + N)
+    for key, power in (("x", x), ("B", b)):
+        v = d[key].float() * 2.0 ** max(power, -126) * 2.0 ** min(power + 126, 0)
+        v.view(-1)[::5 if key == "x" else 7] = 0.0
+        d[key] = v.to(torch.bfloat16)
+    d["h0"].zero_()
+    h, ref = _both(d, L)
+    assert torch.equal(h, ref) and h.isfinite().all() and (h != 0).any()
