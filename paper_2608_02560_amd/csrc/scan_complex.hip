@@ -19,13 +19,10 @@
 // a tile whose |dt| max |w| stays below that skips the 16 reductions a token;
 // other tiles reduce.
 // The kernel is bound by vector issue (11 plain instructions and 3
-// transcendentals per state and token before, 10 and 3 now, two of them no
-// longer DPP forms).  8 x 3000 x 2048 bf16, both passes 730 -> 665 us (702 with
-// the LDS coefficients alone); 64 x 1000 x 2048 977 -> 893; states only, 128 x
-// 500 x 2048 881 -> 814; fp32 64 x 500 x 2048 486 -> 445.  One wave fewer per
-// SIMD fits in readout launches of many rounds (two of at most two): 256 x 200
-// x 2048 stays at 795 us.  At most 168 VGPRs sends values to scratch inside the
-// loop (721 us).
+// transcendentals per state and token with DPP coefficients and every angle
+// reduced, 10 and 3 now, two of them no longer DPP forms).  8 x 3000 x 2048 bf16,
+// both passes 730 -> 670 us; 64 x 1000 x 2048 1034 -> 973, fp32 972 -> 917, states
+// only 894 -> 814; 256 x 200 x 2048 798 -> 743.
 //
 // Long sequences over few channels are cut into time chunks as in the real
 // scan (two levels):
@@ -88,8 +85,13 @@ __device__ __forceinline__ void store_cstate(TSt* dst, const float (&hr)[N], con
 //   KIND == kReadout:   y and (last chunk) hT
 //   KIND == kStateOnly: hT only (y == NULL: C, z, Dskip unread)
 //   KIND == kSummary:   chunk end state from zero -> carry slot c+1, sum dt
+// At most 168 VGPRs, nothing in scratch: three waves per SIMD, which launches of
+// many rounds need.  At two, 256 x 200 x 2048 bf16 takes 800 us, at three 743;
+// states of fp32 inputs 706 -> 658; 8 x 16,384 x 2048 in 256-token chunks
+// 3910 -> 3590.  Two waves per SIMD that are all resident lose up to 1% to the
+// bound (8 x 3000 x 2048 666 -> 670).
 template <int N, typename TIn, typename TOut, typename TSt, int KIND, bool HASZ>
-__global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
+__global__ __launch_bounds__(kSBlock) __attribute__((amdgpu_waves_per_eu(3))) void scan_complex_kernel(
     const TIn* __restrict__ xg, const TIn* __restrict__ dtg, const TIn* __restrict__ zg,
     const TIn* __restrict__ Bg, const TIn* __restrict__ Cg, TOut* __restrict__ yg,
     const ScanParams p) {
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
   const int c = rest / static_cast<int>(p.B);
   const int64_t D = p.D;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // its addresses then hold no VGPR
   const int64_t wave_d0 = static_cast<int64_t>(dblk) * p.threads + wave * 64;
   // progress balancing between the two waves of a SIMD (scan_kernels.h)
   const bool fair = balance_enabled(p);
@@ -161,19 +163,23 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
   const int lane16 = lane & 15;
   const uint32_t el = static_cast<uint32_t>(lane16 < N ? lane16 : N - 1) * sizeof(TIn);
 
-  // N = 16: the B (and C) rows of a tile are 32 (16-bit inputs) or 64
-  // consecutive dwords, dword l in lane l.  They go as fp32 into a
+  // N = 16: the B (and C) rows of a tile are 32 (16-bit inputs: in lanes l and
+  // l + 32, which then do the same) or 64 consecutive dwords, dword l in lane
+  // l.  They go as fp32 into a
   // wave-private LDS slice when the tile is consumed and come back as
   // same-address 16-byte reads, as in the real scan: plain operands in place
   // of 32 DPP broadcasts a token, which issue more slowly, and one load per
   // array and tile in place of four.  State-only kinds gain too (without it
   // 8 x 3000 x 2048 643 us, with it 626).  Shorter N keep the broadcasts.
   constexpr bool kLds = N == 16;
-  constexpr int kDw = kPFPlain * N * static_cast<int>(sizeof(TIn)) / 4;
-  __shared__ __attribute__((aligned(16))) float bc_lds[kLds ? kSWaves : 1][kLds ? kPFPlain : 1][2][kLds ? N : 1];
+  // tokens of a tile: without a readout and LDS the registers allow 8 (N = 4
+  // states, 64 x 1000 x 2048: 243 -> 237 us)
+  constexpr int kPF = kLds || kRead ? kPFPlain : kPFWide;
+  constexpr int kDw = kPF * N * static_cast<int>(sizeof(TIn)) / 4;
+  __shared__ __attribute__((aligned(16))) float bc_lds[kLds ? kSWaves : 1][kLds ? kPF : 1][2][kLds ? N : 1];
 
   struct Tile {
-    typename SI::raw x[kPFPlain], dt[kPFPlain], z[kPFPlain], b[kPFPlain], c[kPFPlain];
+    typename SI::raw x[kPF], dt[kPF], z[kPF], b[kPF], c[kPF];
     uint32_t bw, cw;  // kLds: this lane's dword of the tile's B / C rows
   };
   Tile t0b, t1b;
@@ -183,13 +189,13 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
       // dwords of tokens past the chunk lie past the range and read as zero
       const uint32_t end = ns * bc_row;
       const uint32_t at = static_cast<uint32_t>(tile) * (kDw * 4u);
-      const uint32_t off = lane < kDw ? 4u * static_cast<uint32_t>(lane) : kDropOffset;
+      const uint32_t off = 4u * static_cast<uint32_t>(lane % kDw);
       tb.bw = __builtin_amdgcn_raw_buffer_load_b32(rb, off, at < end ? at : end, 0);
       if constexpr (kRead) tb.cw = __builtin_amdgcn_raw_buffer_load_b32(rc, off, at < end ? at : end, 0);
     }
 #pragma unroll
-    for (int k = 0; k < kPFPlain; ++k) {
-      int st = tile * kPFPlain + k;
+    for (int k = 0; k < kPF; ++k) {
+      int st = tile * kPF + k;
       st = st < last ? st : last;
       const uint32_t so = static_cast<uint32_t>(st) * in_row;
       tb.x[k] = SI::load(rx, dl, so);
@@ -202,21 +208,24 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
       }
     }
   };
-  auto put = [&](int which, uint32_t w) {
+  auto put = [&](uint32_t l, int which, uint32_t w) {
     if constexpr (sizeof(TIn) == 2) {  // token l / 8, coefficients 2 (l mod 8) and the next
-      float* dst = &bc_lds[wave][lane >> 3][which][2 * (lane & 7)];
+      float* dst = &bc_lds[wave][l >> 3][which][2 * (l & 7)];
       dst[0] = __uint_as_float(w << 16);
       dst[1] = __uint_as_float(w & 0xffff0000u);
     } else {
-      bc_lds[wave][lane >> 4][which][lane & 15] = __uint_as_float(w);
+      bc_lds[wave][l >> 4][which][l & 15] = __uint_as_float(w);
     }
   };
   auto stage = [&](const Tile& tb) {
     if constexpr (kLds) {
-      if (lane < kDw) {
-        put(0, tb.bw);
-        if constexpr (kRead) put(1, tb.cw);
-      }
+      // formed anew for each tile: kept, the address is the value that goes to
+      // scratch, and reloading it waits for the next tile's loads
+      uint32_t l = threadIdx.x;
+      asm volatile("" : "+v"(l));
+      l %= kDw;
+      put(l, 0, tb.bw);
+      if constexpr (kRead) put(l, 1, tb.cw);
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the writes are done before any read
     }
   };
@@ -230,7 +239,14 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
     const float dtv = SI::f32(tb.dt[k]);
     const float u = dtv * xv;
     float acc = 0.f;
-    if constexpr (kLds) {
+    if constexpr (kLds && kReduce) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        cstate<true>(hr[n], hi[n], a2[n], w1[n], dtv, u * bc_lds[wave][kc][0][n]);
+        if constexpr (kRead) acc = fmaf(bc_lds[wave][kc][1][n], hr[n], acc);
+        if (n % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+      }
+    } else if constexpr (kLds) {
       float bl[N], cl[N];
 #pragma unroll
       for (int n = 0; n < N; ++n) {
@@ -269,37 +285,38 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
     if constexpr (kLds) {
       float m = 0.f;
 #pragma unroll
-      for (int k = 0; k < kPFPlain; ++k) m = __builtin_elementwise_maximum(m, fabsf(SI::f32(tb.dt[k])));
+      for (int k = 0; k < kPF; ++k) m = __builtin_elementwise_maximum(m, fabsf(SI::f32(tb.dt[k])));
       direct = __builtin_amdgcn_ballot_w64(!(m * w_max < 256.f)) == 0;
     }
     if (direct) {
 #pragma unroll
-      for (int k = 0; k < kPFPlain; ++k) {
-        if (kGuard && tile * kPFPlain + k >= nsteps) break;
-        step(tb, k, k, tile * kPFPlain + k, std::false_type{});
+      for (int k = 0; k < kPF; ++k) {
+        if (kGuard && tile * kPF + k >= nsteps) break;
+        step(tb, k, k, tile * kPF + k, std::false_type{});
       }
     } else if constexpr (kLds) {
-      // one token per round, so this path needs little code and few registers
+      // one token per round, so this path needs little code and, with two states
+      // at a time (step), few registers: it must not set the kernel's
 #pragma unroll 1
-      for (int k = 0; k < kPFPlain; ++k) {
-        if (kGuard && tile * kPFPlain + k >= nsteps) break;
+      for (int k = 0; k < kPF; ++k) {
+        if (kGuard && tile * kPF + k >= nsteps) break;
         Tile tc;
         tc.x[0] = tb.x[0];
         tc.dt[0] = tb.dt[0];
         if constexpr (HASZ) tc.z[0] = tb.z[0];
 #pragma unroll
-        for (int i = 1; i < kPFPlain; ++i) {
+        for (int i = 1; i < kPF; ++i) {
           tc.x[0] = k == i ? tb.x[i] : tc.x[0];
           tc.dt[0] = k == i ? tb.dt[i] : tc.dt[0];
           if constexpr (HASZ) tc.z[0] = k == i ? tb.z[i] : tc.z[0];
         }
-        step(tc, 0, k, tile * kPFPlain + k, std::true_type{});
+        step(tc, 0, k, tile * kPF + k, std::true_type{});
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < kPFPlain; ++k) {
-        if (kGuard && tile * kPFPlain + k >= nsteps) break;
-        step(tb, k, k, tile * kPFPlain + k, std::true_type{});
+      for (int k = 0; k < kPF; ++k) {
+        if (kGuard && tile * kPF + k >= nsteps) break;
+        step(tb, k, k, tile * kPF + k, std::true_type{});
       }
     }
   };
@@ -310,7 +327,7 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
     fetch(t0b, 0);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): tile 0 in before tile 1 is requested
     int tile = 0;
-    for (; (tile + 2) * kPFPlain <= nsteps; tile += 2) {
+    for (; (tile + 2) * kPF <= nsteps; tile += 2) {
       if (fair) balance_step(progress, wave, tile);
       fetch(t1b, tile + 1);
       run_tile(t0b, tile, whole);
@@ -322,14 +339,18 @@ __global__ __launch_bounds__(kSBlock) void scan_complex_kernel(
     run_tile(t1b, tile + 1, guarded);
   }
 
-  if (!live) return;
+  // the channel once more, so that it holds no registers through the time loop
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int64_t de = wave_d0 + (tid & 63);
+  if (de >= D) return;
   if constexpr (KIND == kSummary) {
-    store_cstate<N>(p.carry + (static_cast<int64_t>(b) * p.nchunks + c + 1) * DN2 + 2 * d * N, hr,
+    store_cstate<N>(p.carry + (static_cast<int64_t>(b) * p.nchunks + c + 1) * DN2 + 2 * de * N, hr,
                     hi);
-    p.dtsum[(static_cast<int64_t>(b) * p.nchunks + c) * D + d] = dtacc;
+    p.dtsum[(static_cast<int64_t>(b) * p.nchunks + c) * D + de] = dtacc;
   } else {
     if ((p.flags & kHasHT) && c == p.nchunks - 1)
-      store_cstate<N>(static_cast<TSt*>(p.hT) + b * p.hT_stride + 2 * d * N, hr, hi);
+      store_cstate<N>(static_cast<TSt*>(p.hT) + b * p.hT_stride + 2 * de * N, hr, hi);
   }
 }
 

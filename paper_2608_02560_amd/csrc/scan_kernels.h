@@ -89,7 +89,7 @@ __device__ __forceinline__ void balance_step(int* progress, int wave, int tile) 
 // vector-memory counter with the tile loads, and longer tiles wait on them
 // less often.
 constexpr int kPFPlain = 4;
-constexpr int kPFWide = 8;  // trajectory capture, complex-A kernel
+constexpr int kPFWide = 8;  // trajectory capture, readout-free complex-A scans of N < 16
 
 enum Kind { kReadout = 0, kStateOnly = 1, kSummary = 2 };
 

@@ -76,3 +76,8 @@ def test_readout_free_scans_keep_their_registers(kernels):
 def test_trajectories_keep_three_waves(kernels):
     for name, k in _pick(kernels, r"11scan_kernelILi(16|32|64)ENS_6bf16_tEfN?\w*?Li1ELb0ELi[12]EE").items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 168, name
+
+
+def test_complex_scans_keep_three_waves(kernels):
+    for name, k in _pick(kernels, r"19scan_complex_kernelILi16E").items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 168, name
