@@ -333,8 +333,16 @@ constexpr int kFewWaves = 4;
 constexpr int kFewQ = 32;
 constexpr int kFewMaxE = 1024;  // kFewWaves x 16 steps of 16 features
 
+// Workgroups of an instance that a CU holds, by its registers: unprepared keys of
+// 8 steps keep 16 loads of 16 bytes in flight per lane in 157 VGPRs, three
+// workgroups.  Bound to 128 they reloaded spilled values between the loads of a
+// block, which waited for those in flight: 16 x 100,003 x 384 54.8 -> 48.9 us
+// (and 49.8 with half the loads in flight at four workgroups).
 template <bool PREP, int NS>
-__global__ __launch_bounds__(64 * kFewWaves, NS <= 8 ? 4 : 2) void screen_few_kernel(const RetrieveParams p) {
+constexpr int kFewPerCu = NS > 8 ? 2 : NS == 8 && !PREP ? 3 : 4;
+
+template <bool PREP, int NS>
+__global__ __launch_bounds__(64 * kFewWaves, (kFewPerCu<PREP, NS>)) void screen_few_kernel(const RetrieveParams p) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r32 = lane & 31;

@@ -81,3 +81,13 @@ def test_trajectories_keep_three_waves(kernels):
 def test_complex_scans_keep_three_waves(kernels):
     for name, k in _pick(kernels, r"19scan_complex_kernelILi16E").items():
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_count"] <= 168, name
+
+
+def test_the_few_query_screen_fits_as_often_as_it_is_launched(kernels):
+    """No scratch in the block loop, and registers and LDS for the workgroups of
+    four waves per CU that the launch counts on ({prepared, steps}: number)."""
+    per_cu = {(1, 2): 4, (1, 8): 4, (1, 16): 2, (0, 2): 4, (0, 8): 3, (0, 16): 2}
+    for (prep, steps), n in per_cu.items():
+        (k,) = _pick(kernels, r"17screen_few_kernelILb%dELi%dEE" % (prep, steps)).values()
+        assert k[".private_segment_fixed_size"] == 0
+        assert 512 // (-(-k[".vgpr_count"] // 8) * 8) >= n and 163840 // k[".group_segment_fixed_size"] >= n
