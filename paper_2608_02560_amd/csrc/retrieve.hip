@@ -17,7 +17,8 @@
 //            32-key block) it keeps the largest screen score S~, its key, and
 //            the largest S~ of the block's other keys; and the squared norm
 //            of every key and the largest one of every block.
-//   decide   one wave per query (four for top-k and large indexes): m = the largest screen score.  A key can
+//   decide   one wave per query (four for top-k and large indexes): m = the
+//            largest screen score.  A key can
 //            still be the fp64 maximum only if S~_i + e(i) >= m - e(i0), where
 //            e(i) = g |q| |k_i| + h (|q| + |k_i|) + tiny bounds the error of
 //            its screen score (g bounds the fp16 rounding and the fp32
@@ -327,8 +328,8 @@ __global__ __launch_bounds__(64 * kRetWaves) void screen_kernel(const RetrievePa
 // in LDS (two buffers, one barrier per block), where one wave, another one
 // for each block, forms the block's summary.  Any split of the fp32 sum stays
 // within the margin's 2 gamma_E.  Bound by the key stream: several workgroups
-// per CU keep it going.  16 x 100,003 x 384 prepared: rounding and screen
-// 3.0 + 27.9 -> 21.8 us (3.5 TB/s); 4 x 3,000: 3 + 8 -> 4.8 us.
+// per CU keep it going.  Top-3 of 16 x 100,003 x 384: prepared 70 -> 31.6 us,
+// unprepared 92 -> 44; of 32 x 3,000: 23.7 -> 17.5 and 25.3 -> 19.
 constexpr int kFewWaves = 4;
 constexpr int kFewQ = 32;
 constexpr int kFewMaxE = 1024;  // kFewWaves x 16 steps of 16 features
@@ -336,10 +337,22 @@ constexpr int kFewMaxE = 1024;  // kFewWaves x 16 steps of 16 features
 // Workgroups of an instance that a CU holds, by its registers: unprepared keys of
 // 8 steps keep 16 loads of 16 bytes in flight per lane in 157 VGPRs, three
 // workgroups.  Bound to 128 they reloaded spilled values between the loads of a
-// block, which waited for those in flight: 16 x 100,003 x 384 54.8 -> 48.9 us
-// (and 49.8 with half the loads in flight at four workgroups).
+// block, which waited for those in flight: top-3 of 16 x 100,003 x 384 54.8 ->
+// 49.2 us (and 49.8 with half the loads in flight at four workgroups).
 template <bool PREP, int NS>
 constexpr int kFewPerCu = NS > 8 ? 2 : NS == 8 && !PREP ? 3 : 4;
+
+// Every workgroup of the launch resident at once, the blocks dealt to them in
+// turn, so that none has more than one block above another.  (About five per CU,
+// each with the same number of consecutive blocks, left a second round for all
+// but the smallest kernel and gave some CUs a quarter more than the mean: 16 x
+// 100,003 x 384 prepared 33.9 -> 31.6 us, unprepared 49.2 -> 44.3; 32 x 33,000 x
+// 1024 prepared 53.6 -> 42.2.)
+template <bool PREP, int NS>
+dim3 few_grid(int64_t blocks) {
+  constexpr int64_t kPlaces = 256 * kFewPerCu<PREP, NS>;
+  return dim3(static_cast<unsigned>(blocks < kPlaces ? blocks : kPlaces));
+}
 
 template <bool PREP, int NS>
 __global__ __launch_bounds__(64 * kFewWaves, (kFewPerCu<PREP, NS>)) void screen_few_kernel(const RetrieveParams p) {
@@ -555,21 +568,17 @@ static void error_bound_constants(RetrieveParams& p) {
 hipError_t launch_retrieve_screen(RetrieveParams& p, hipStream_t s) {
   error_bound_constants(p);
   if (p.nkb > 0 && p.Q <= kFewQ && p.E <= kFewMaxE) {
-    // Blocks per workgroup such that about five workgroups per CU share them
-    // evenly.
-    const int64_t each = (p.nkb + 1279) / 1280;
-    const dim3 grid(static_cast<unsigned>((p.nkb + each - 1) / each));
     const dim3 block(64 * kFewWaves);
     const bool prep = p.kop != nullptr;
     if (p.nks <= 2 * kFewWaves) {
-      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 2>), grid, block, 0, s, p);
-      else hipLaunchKernelGGL((screen_few_kernel<false, 2>), grid, block, 0, s, p);
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 2>), (few_grid<true, 2>(p.nkb)), block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 2>), (few_grid<false, 2>(p.nkb)), block, 0, s, p);
     } else if (p.nks <= 8 * kFewWaves) {
-      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 8>), grid, block, 0, s, p);
-      else hipLaunchKernelGGL((screen_few_kernel<false, 8>), grid, block, 0, s, p);
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 8>), (few_grid<true, 8>(p.nkb)), block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 8>), (few_grid<false, 8>(p.nkb)), block, 0, s, p);
     } else {
-      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 16>), grid, block, 0, s, p);
-      else hipLaunchKernelGGL((screen_few_kernel<false, 16>), grid, block, 0, s, p);
+      if (prep) hipLaunchKernelGGL((screen_few_kernel<true, 16>), (few_grid<true, 16>(p.nkb)), block, 0, s, p);
+      else hipLaunchKernelGGL((screen_few_kernel<false, 16>), (few_grid<false, 16>(p.nkb)), block, 0, s, p);
     }
   } else if (p.nkb > 0) {
     const int64_t entries = static_cast<int64_t>(p.nqg) * p.nks * 64;
