@@ -11,6 +11,7 @@
 #include <cstring>
 
 #include "precog_kernels.h"
+#include "scan_shape.h"
 
 namespace {
 
@@ -46,125 +47,14 @@ bool valid_n(int64_t n) {
 }
 
 constexpr int64_t kBlock = precog::kScanThreads;  // lanes per scan workgroup (real and complex A)
-constexpr int64_t kHalfBlock = kBlock / 2;
-constexpr int64_t kCus = 256;             // compute units of the MI355X
-constexpr int64_t kTargetWaves = 2048;    // 2 waves per SIMD on 256 CUs
-constexpr int64_t kMinAutoChunk = 8;
+constexpr int64_t kCus = precog::kShapeCus;
+static_assert(kBlock == precog::kShapeBlock, "the larger workgroup");
 
-int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// Longest chunk whose per-token streams stay addressable with the kernels'
-// 32-bit buffer offsets: x, dt, z, y take D elements per token and B, C take
-// N, at most 4 bytes each, so chunk * max(D, N) * 4 < 2^31.
-int64_t max_chunk(const precog_scan_desc* d) {
-  const int64_t w = d->dim > d->dstate ? d->dim : d->dstate;
-  const int64_t row = (w > 0 ? w : 1) * 4;
-  return ((1LL << 31) - 1) / row;
-}
-
-int64_t lanes_per_row(const precog_scan_desc* d) {
-  return d->dim * (d->dstate > 16 ? d->dstate / 16 : 1);
-}
-
-// How a scan is launched: tokens per time chunk and threads per workgroup.
-struct ScanShape {
-  int64_t chunk, threads;
-};
-
-// Time of a pass over one token, in ns, with `groups` workgroups: all of them
-// run side by side, so the fullest SIMD sets it.  A workgroup puts one
-// (kHalfBlock threads) or two (kBlock) waves on each SIMD of its CU.
-// Measured, one pass of 1024 tokens, readout with gate, bf16: one wave per
-// SIMD 275, two 365, three 553, four 758-793 (fp32 308 / 375; N = 64 states
-// only 212 / 288 / 443 / 563; complex A 550 / 975): two waves cost 1.33
-// (1.77) times one, every further wave half of two.
-struct ScanRate {
-  double one, two;
-};
-constexpr ScanRate kRealRate{275.0, 365.0}, kComplexRate{550.0, 975.0};
-double token_ns(int64_t groups, int64_t threads, const ScanRate& r) {
-  const int64_t w = ceil_div(groups, kCus) * (threads == kBlock ? 2 : 1);
-  return w == 1 ? r.one : 0.5 * r.two * static_cast<double>(w);
-}
-
-// The smaller workgroup where it leaves the fullest SIMD less to do (up to
-// 1024 waves, one per SIMD: 365 -> 275 ns a token; 2304 waves 661 -> 554),
-// the larger one, whose waves are balanced in pairs, where both are equal
-// (1280 waves 368 against 393) and in launches of more than one round.
-int64_t pick_threads(const precog_scan_desc* d, int64_t nchunks) {
-  const int64_t big = d->batch * ceil_div(lanes_per_row(d), kBlock) * nchunks;
-  const int64_t small = d->batch * ceil_div(lanes_per_row(d), kHalfBlock) * nchunks;
-  return small <= 4 * kCus && ceil_div(small, kCus) < 2 * ceil_div(big, kCus) ? kHalfBlock : kBlock;
-}
-
-// Chunks for which a descriptor's workspace is sized: time may be cut when
-// batch x channel waves alone do not fill two waves on every SIMD, into at
-// most as many chunks as do.
-int64_t reserve_chunks(const precog_scan_desc* d) {
-  const int64_t L = d->seqlen;
-  const int64_t waves = d->batch * ceil_div(lanes_per_row(d), 64);
-  if (waves >= kTargetWaves || L <= 2 * kMinAutoChunk) return 1;
-  int64_t nch = ceil_div(kTargetWaves, waves > 0 ? waves : 1);
-  const int64_t max_nch = L / kMinAutoChunk;
-  if (nch > max_nch) nch = max_nch;
-  return nch < 1 ? 1 : nch;
-}
-
-// Auto policy: of one pass and of the cuts that fill every CU once with the
-// one or the other workgroup size, the one whose passes are expected to be
-// over first.  A cut pays for a second, readout-free pass over all chunks but
-// the last (0.72 of a pass: 69 of 92 vector instructions a token) and about
-// 10 us for two more launches.  Filling to just past a whole number of
-// workgroups per CU is what this avoids: 5 x 1237 x 1000 in 26 chunks is 260
-// workgroups (60.5 us), in 25 it is 250 (48.8 us).
-ScanShape auto_shape(const precog_scan_desc* d, const ScanRate& r) {
-  const int64_t L = d->seqlen;
-  const int64_t most = reserve_chunks(d);
-  ScanShape best{L, pick_threads(d, 1)};
-  if (most <= 1) return best;
-  const int64_t lanes = lanes_per_row(d);
-  double best_ns =
-      static_cast<double>(L) * token_ns(d->batch * ceil_div(lanes, best.threads), best.threads, r);
-  for (const int64_t threads : {kBlock, kHalfBlock}) {
-    const int64_t row_groups = d->batch * ceil_div(lanes, threads);
-    int64_t n = kCus / (row_groups > 0 ? row_groups : 1);
-    if (n > most) n = most;
-    if (n < 2) continue;
-    const int64_t chunk = ceil_div(L, n);
-    const int64_t nch = ceil_div(L, chunk);
-    const double ns = 1e4 + static_cast<double>(chunk) * (0.72 * token_ns(row_groups * (nch - 1), threads, r) +
-                                                          token_ns(row_groups * nch, threads, r));
-    if (ns < best_ns) {
-      best_ns = ns;
-      best = ScanShape{chunk, threads};
-    }
-  }
-  return best;
-}
-
-// Chunk length and workgroup size used for a descriptor (after validation).
-ScanShape scan_shape(const precog_scan_desc* d, const ScanRate& r) {
-  const int64_t L = d->seqlen;
-  if (L <= 0) return ScanShape{1, kBlock};
-  const int64_t cap = max_chunk(d);
-  ScanShape s{d->chunk, kBlock};
-  if (d->chunk <= 0) s = auto_shape(d, r);
-  if (s.chunk > L) s.chunk = L;
-  const bool cut = s.chunk > cap;
-  if (cut) s.chunk = cap;
-  if (d->chunk > 0 || cut) s.threads = pick_threads(d, ceil_div(L, s.chunk));
-  return s;
-}
-
-// Chunks the workspace of a descriptor is sized for: those of its shape, or
-// those an automatic cut may take if that is more.
-int64_t workspace_chunks(const precog_scan_desc* d, const ScanRate& r) {
-  if (d->seqlen <= 0) return 1;
-  const int64_t n = ceil_div(d->seqlen, scan_shape(d, r).chunk);
-  if (d->chunk > 0) return n;
-  const int64_t m = ceil_div(d->seqlen, ceil_div(d->seqlen, reserve_chunks(d)));
-  return n > m ? n : m;
-}
+using precog::ceil_div;
+using precog::lanes_per_row;
+using precog::scan_shape;
+using precog::ScanShape;
+using precog::workspace_chunks;
 
 size_t align_up(size_t v) { return (v + 255) & ~static_cast<size_t>(255); }
 
@@ -224,7 +114,7 @@ const char* precog_status_string(precog_status s) {
 
 size_t precog_scan_workspace_bytes(const precog_scan_desc* desc) {
   if (validate_desc(desc) != PRECOG_OK) return 0;
-  return scan_ws(desc, workspace_chunks(desc, kRealRate)).total;
+  return scan_ws(desc, workspace_chunks(desc)).total;
 }
 
 }  // extern "C"
@@ -273,11 +163,11 @@ precog_status scan_prepare(const precog_scan_desc* desc, const void* x, const vo
   for (const void* p : ptrs)
     if (p && !aligned16(p)) return PRECOG_ERR_ALIGN;
 
-  const ScanShape shape = scan_shape(desc, kRealRate);
+  const ScanShape shape = scan_shape(desc, false);
   const int64_t chunk = shape.chunk, threads = shape.threads;
   const int64_t nchunks = work ? ceil_div(L, chunk) : 1;
   if (nchunks > (1LL << 20)) return PRECOG_ERR_SHAPE;
-  const size_t need = scan_ws(desc, work ? workspace_chunks(desc, kRealRate) : 1).total;
+  const size_t need = scan_ws(desc, work ? workspace_chunks(desc) : 1).total;
   if (need > 0 && (!workspace || workspace_bytes < need)) return PRECOG_ERR_WORKSPACE;
   const ScanWs ws = scan_ws(desc, nchunks);
   const int64_t dblocks = ceil_div(lanes_per_row(desc), threads);
@@ -872,7 +762,7 @@ ScanWs complex_ws(const precog_scan_desc* d, int64_t nchunks) {
 
 size_t precog_scan_complex_workspace_bytes(const precog_scan_desc* desc) {
   if (validate_complex_desc(desc) != PRECOG_OK) return 0;
-  return complex_ws(desc, workspace_chunks(desc, kComplexRate)).total;
+  return complex_ws(desc, workspace_chunks(desc)).total;
 }
 
 precog_status precog_scan_complex(const precog_scan_desc* desc, const void* x, const void* dt,
@@ -892,11 +782,11 @@ precog_status precog_scan_complex(const precog_scan_desc* desc, const void* x, c
   const void* ptrs[] = {x, dt, A_re, A_im, B, C, z, Dskip, h0, y, hT, workspace};
   for (const void* p : ptrs)
     if (p && !aligned16(p)) return PRECOG_ERR_ALIGN;
-  const ScanShape shape = scan_shape(desc, kComplexRate);
+  const ScanShape shape = scan_shape(desc, true);
   const int64_t chunk = shape.chunk, threads = shape.threads;
   const int64_t nchunks = work ? ceil_div(L, chunk) : 1;
   if (nchunks > (1LL << 20)) return PRECOG_ERR_SHAPE;
-  const size_t need = complex_ws(desc, work ? workspace_chunks(desc, kComplexRate) : 1).total;
+  const size_t need = complex_ws(desc, work ? workspace_chunks(desc) : 1).total;
   if (need > 0 && (!workspace || workspace_bytes < need)) return PRECOG_ERR_WORKSPACE;
   const ScanWs ws = complex_ws(desc, nchunks);
   const int64_t dblocks = ceil_div(D, threads);

@@ -44,6 +44,7 @@
 #include "compose.h"
 #include "decide.h"
 #include "precog_kernels.h"
+#include "scan_shape.h"
 
 namespace precog {
 namespace {
@@ -1133,9 +1134,6 @@ __global__ __launch_bounds__(256) void carry_kernel(const ScanParams p, int N) {
 // rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2 and 3), so every
 // carry needs one round trip instead of one per batch of chunks.  The same
 // carries as carry_kernel up to fp32 reassociation.
-constexpr int kCarryScanMaxChunks = 64;
-constexpr int64_t kCarryScanMaxLanes = 8192;  // (b, d, n) lanes: waves of strided loads
-
 template <int CTRL, int ROWS>
 __device__ __forceinline__ void affine_step(float& m, float& s) {
   // lanes without a source keep the identity step (1, 0)
@@ -1218,7 +1216,7 @@ hipError_t launch_typed(const ScanParams& p, hipStream_t s) {
                        static_cast<const TIn*>(p.z), static_cast<const TIn*>(p.Bm),
                        static_cast<const TIn*>(p.Cm), static_cast<float*>(nullptr), p);
     const int64_t lanes = p.B * p.D * N;
-    if (p.nchunks > 8 && p.nchunks <= kCarryScanMaxChunks && lanes <= kCarryScanMaxLanes)
+    if (carry_scan(p.nchunks, lanes))
       hipLaunchKernelGGL((carry_scan_kernel<TSt>), dim3(static_cast<unsigned>((lanes * 64 + 255) / 256)),
                          dim3(256), 0, s, p, N);
     else
