@@ -94,12 +94,18 @@ typedef struct {
                                  in its layer slot of a [chunks, layers, D, N]
                                  store) */
     int64_t chunk;            /* time-chunk length of the two-level scan:
-                                 0 = chosen by the library; >= L = one pass */
+                                 0 = chosen by the library from the descriptor
+                                 alone; >= L = one pass */
 } precog_scan_desc;
 
-/* Bytes of device workspace precog_scan_encode needs for `desc` (0 when the
- * scan runs in one pass).  Returns 0 for an invalid descriptor too; the
- * encode call reports the error. */
+/* Bytes of device workspace precog_scan_encode asks for: with a requested
+ * chunk, what its chunks need (0 for one pass); with chunk = 0, what the most
+ * chunks need that the library may choose, which are those of at least 8
+ * tokens that fill 2048 waves.  A scan that then runs in one pass leaves the
+ * workspace untouched, but the call still checks for it, so the size does not
+ * depend on how the choice is made; it is 0 for scans of 2048 waves and more
+ * and of up to 16 tokens.  Returns 0 for an invalid descriptor too; the encode
+ * call reports the error. */
 size_t precog_scan_workspace_bytes(const precog_scan_desc *desc);
 
 /* The recurrence of Eq. 1 (Sec. 3) with a real, positive diagonal A, rolled
@@ -209,17 +215,17 @@ precog_status precog_scan_trajectory(const precog_scan_desc *desc,
  *   h0, hT      complex state rows [D, N, 2] ((real, imaginary) interleaved)
  *               in desc->state_dtype; batch strides in elements, 0 = 2*D*N.
  *   desc->dstate in {1, 2, 4, 8, 16}.
- *   Time chunks as in precog_scan_encode (desc->chunk, 0 = automatic: one
- *               pass when batch x channels fill the GPU; chunks are capped
- *               so that chunk * max(D, N) * 4 < 2^31).  A chunked scan folds
- *               the chunks' end states with the product of their decays,
- *               exp(-(A_re + i A_im) sum dt) (its angle reduced in fp64),
- *               and replays each chunk from its carried-in state.
- *   workspace   precog_scan_complex_workspace_bytes(desc) bytes (0 for one
- *               pass: NULL allowed), 16-byte aligned; about
- *               B * chunks * D * (8 N + 4) bytes.
- * The rotation uses the hardware sine and cosine of the angle reduced to
- * [0, 1) revolutions; the magnitude uses the hardware exp2. */
+ *   Time chunks as in precog_scan_encode (desc->chunk, 0 = automatic; chunks
+ *               are capped so that chunk * max(D, N) * 4 < 2^31).  A chunked
+ *               scan folds the chunks' end states with the product of their
+ *               decays, exp(-(A_re + i A_im) sum dt) (its angle reduced in
+ *               fp64), and replays each chunk from its carried-in state.
+ *   workspace   precog_scan_complex_workspace_bytes(desc) bytes (sized as
+ *               precog_scan_workspace_bytes; NULL allowed where it is 0),
+ *               16-byte aligned; about B * chunks * D * (8 N + 4) bytes.
+ * The rotation uses the hardware sine and cosine, of the angle itself up to
+ * 256 revolutions and of the angle reduced to [0, 1) revolutions beyond; the
+ * magnitude uses the hardware exp2. */
 size_t precog_scan_complex_workspace_bytes(const precog_scan_desc *desc);
 
 precog_status precog_scan_complex(const precog_scan_desc *desc, const void *x,
