@@ -144,8 +144,8 @@ def _stream(stream):
 
 
 def _row_elems(t):
-    """Elements of one row of t (at least one row), without a view of it."""
-    return t.numel() // t.shape[0]
+    """Elements of one row of t, without a view of it; no row: t[0]'s IndexError."""
+    return t.numel() // t.shape[0] if t.shape[0] else t[0].numel()
 
 
 def _check(fn, st):

@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2608_02560_amd import precog as P
 
@@ -406,3 +407,13 @@ def test_descriptor_layout_matches_header():
     # int64 x4, three 4-byte enums (+4 padding), int64 x3
     assert ctypes.sizeof(P.ScanDesc) == 4 * 8 + 3 * 4 + 4 + 3 * 8
     assert P.ScanDesc.h0_batch_stride.offset == 48
+
+
+def test_injection_without_any_row_is_an_index_error():
+    """Neither a store nor an h0 row tells the row size."""
+    none = torch.empty(0, 4, 4)
+    idx = torch.empty(0, dtype=torch.int32)
+    with pytest.raises(IndexError):
+        P.inject_gather(none, idx, none)
+    with pytest.raises(IndexError):
+        P.inject_compose(none, idx[:, None], torch.empty(0, 1, dtype=torch.float64), 0.1, none)
