@@ -408,9 +408,9 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
 // carries one token (P = 1: four tokens share a u operand) or, for P > 1, one
 // of the two state groups that lanes 0-15 and 16-31 of a half hold.
 // These kinds are bound by vector issue: 69 instructions a token before, 57
-// now and one matrix instruction, which takes 20-30 cycles of it (16 output
-// registers).  Long context (2 x 65,536 x 2048, both passes) 1442 -> 1311
-// us, N = 64 states (96 x 3000 x 1536) 3925 -> 3705 us.  With a readout the
+// now (58 for N = 64) and one matrix instruction, which takes 20-30 cycles of it
+// (16 output registers).  Long context (2 x 65,536 x 2048, both passes) 1462 ->
+// 1320 us, N = 64 states (96 x 3000 x 1536) 3915 -> 3800 us.  With a readout the
 // gain is 2-3% at two waves per SIMD and the registers for C_t beside the
 // products cost the four-wave launches a wave (query prefill 43 -> 54 us), so
 // that kind keeps its multiplications, and so does the one-call query kernel,
@@ -419,8 +419,8 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
 // a non-finite u or B takes the multiplications instead, and so does one with
 // a nonzero u or B below 2^-62 (MxRange), so that every result is the
 // multiplications'.  The test of the small ones takes 4 instructions a tile:
-// states of 96 x 1000 x 1536, N = 64, 1232 -> 1254 us; with zeros in
-// nearly every tile 1310 (x) to 1385 us (B).
+// states of 96 x 1000 x 1536, N = 64, 1232 -> 1254 us (1307 by multiplications
+// alone); with zeros in nearly every tile 1320 (x) to 1390 us (B).
 typedef float mx_float16 __attribute__((ext_vector_type(16)));
 typedef __bf16 mx_bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t mx_u32x4 __attribute__((ext_vector_type(4)));

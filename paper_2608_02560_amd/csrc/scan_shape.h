@@ -55,7 +55,7 @@ inline ScanRate scan_rate(const precog_scan_desc* d, bool complex) {
 
 // Threads of a workgroup: whole rows of up to four waves (a workgroup with
 // waves past the last channel puts its live ones on the same SIMDs as the
-// next: 2048 rows of 64 channels 723 ns a token with 512 threads, 365 with
+// next: 2048 rows of 64 channels 726 ns a token with 512 threads, 442 with
 // 64), else `large` or half of it.
 inline int64_t group_threads(const precog_scan_desc* d, bool large) {
   const int64_t w = waves_per_row(d);
