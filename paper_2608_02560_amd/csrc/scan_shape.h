@@ -63,9 +63,14 @@ inline int64_t group_threads(const precog_scan_desc* d, bool large) {
 }
 
 // Waves on the fullest SIMD when `chunks` chunks of every row run side by side.
+// Workgroups of one wave spread over a CU's SIMDs (1024 rows of 64 channels 279
+// ns a token), two of two waves do not (512 rows of 128 channels 387, 256 rows
+// 265).
 inline int64_t simd_waves(const precog_scan_desc* d, int64_t threads, int64_t chunks) {
   const int64_t groups = d->batch * ceil_div(lanes_per_row(d), threads) * chunks;
-  return ceil_div(ceil_div(groups, kShapeCus) * (threads / 64), 4);
+  const int64_t per_cu = ceil_div(groups, kShapeCus);
+  const int64_t w = ceil_div(per_cu * (threads / 64), 4);
+  return threads == 128 && per_cu > 1 && w < 2 ? 2 : w;
 }
 
 // The smaller workgroup where it leaves the fullest SIMD less to do (up to
@@ -146,9 +151,10 @@ inline ScanShape auto_shape(const precog_scan_desc* d, bool complex) {
   for (const bool large : {true, false}) {
     const int64_t threads = group_threads(d, large);
     const int64_t row_groups = d->batch * ceil_div(lanes_per_row(d), threads);
-    const int64_t places = kShapeCus * 4 * 64 / threads / (row_groups > 0 ? row_groups : 1);  // one wave per SIMD
-    const int64_t two = kShapeCus * (8 * 64 / threads) / (row_groups > 0 ? row_groups : 1);
-    for (int64_t n : {two, places, static_cast<int64_t>(fold), kCarryScanMaxChunks}) {
+    const int64_t rows = row_groups > 0 ? row_groups : 1;
+    // workgroups on a CU with two waves and with one on a SIMD, and one
+    const int64_t two = kShapeCus * (512 / threads) / rows, one_each = kShapeCus * (256 / threads) / rows;
+    for (int64_t n : {two, one_each, kShapeCus / rows, static_cast<int64_t>(fold), kCarryScanMaxChunks}) {
       if (n > two) n = two;
       if (n > most) n = most;
       if (n < 2) continue;
