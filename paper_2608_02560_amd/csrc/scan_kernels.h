@@ -420,7 +420,8 @@ __device__ __forceinline__ float lane_xor(float v, int m) {
 // a nonzero u or B below 2^-62 (MxRange), so that every result is the
 // multiplications'.  The test of the small ones takes 4 instructions a tile:
 // states of 96 x 1000 x 1536, N = 64, 1232 -> 1254 us (1307 by multiplications
-// alone); with zeros in nearly every tile 1320 (x) to 1390 us (B).
+// alone), fp16 states of 40 x 500 x 1600, N = 16, 130 -> 142 us, the most it
+// costs; with zeros in nearly every tile 1320 (x) to 1390 us (B).
 typedef float mx_float16 __attribute__((ext_vector_type(16)));
 typedef __bf16 mx_bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t mx_u32x4 __attribute__((ext_vector_type(4)));
@@ -958,7 +959,7 @@ __device__ __forceinline__ void scan_body(
         // the kernel's registers.  With all 16 products and exponentials at
         // once it took 133-182 where the products' own path takes 105-159, and
         // the readout-free kinds reloaded spilled addresses in every tile.
-        // N = 16 states 64 x 1000 x 2048, fp32 state 385 -> 280 us; trajectory
+        // N = 16 states 64 x 1000 x 2048, fp32 state 385 -> 300 us; trajectory
         // of 64 states 256 x 200 x 1024, every 64th 505 -> 430 us.
 #pragma unroll 1
         for (int k = 0; k < kPF; ++k) {
